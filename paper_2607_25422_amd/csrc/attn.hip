@@ -8,8 +8,8 @@
 // bf16 path (MFMA): passage-major, only the graph's edges are computed (the
 // kernel comment below); a device-built work list orders the items by cost.
 //
-// fp32 path: one wave per (kept row, head); 64 tokens per step, lane = token
-// for the logits, lane = feature for the PV product.
+// fp32 path: 16 rows per workgroup on the float32 matrix cores (at its
+// kernel).
 #include "skip_common.h"
 #include "skip_internal.h"
 #include "skip_plan.h"
@@ -645,87 +645,205 @@ attn_plan_kernel(const int32_t* __restrict__ kept_offsets,
 }
 
 // ---------------------------------------------------------------------------
-// fp32 path: one wave per (kept row, head).
-template <int D>
-__global__ void __launch_bounds__(256)
+// fp32 path on the float32 matrix cores (v_mfma_f32_16x16x4_f32: float32
+// products and sums).  Workgroup = (question, head, 16 consecutive kept rows)
+// of NW waves, which take the 16-token blocks of the passages adjacent to at
+// least one of the rows in turn (block i to wave i mod NW), each with its own
+// (O, max, sum); they are merged in wave order through LDS at the end, so the
+// loop has no barrier and no LDS access.  Per block:
+//   S^T (16 tokens x 16 rows) = K . Q^T, a logit of a row not adjacent to the
+//   passage at -inf, online softmax in base 2, O^T += V^T . P^T.
+// Both products take their operands as 16-byte loads, in the order the lanes
+// hold them: lane l (r16 = l % 16, g = l / 16) supplies contraction slot g,
+// and which feature (S) or token (O) a slot stands for is free as long as
+// both operands agree.  S: slot g of product m of a 16-feature group is
+// feature 4g + m (one float4 of the row).  O: slot g of product j is token
+// 4g + j of the block, where S^T leaves that logit, and output row f of
+// feature block e is feature 4f + e (one float4 of a token's 64 features), so
+// a lane ends with 16 consecutive features of its row.
+// Bound by the matrix cores at large batches (rows not adjacent to a passage
+// of their tile compute for nothing there; one wave per row and head, edges
+// only, on the vector units spent ten times as long) and by the wave's load
+// and product chain at small ones.  Measured against that form: 8 questions
+// of 96 rows, 16 heads of 64, 5 passages of 97-160 tokens 35.5 us (359); one
+// question of 96 rows, 4 heads of 64, 4 passages of 64 tokens 7.9 us (38.3).
+constexpr int kF32Rows = 16;
+// Workgroups from which four waves each fill the chip; below, eight shorten
+// the wave's chain (routes of 350 to 2304 workgroups: 134 us with four and
+// 111 with eight at the low end, equal within 1.5 % at 768, 154 with eight
+// and 140 with four at the high end).
+constexpr long long kF32Wide = 1024;
+
+template <int D, int NW>
+__global__ void __launch_bounds__(64 * NW)
 attn_f32_kernel(const float* __restrict__ qbase, const int32_t* __restrict__ kept_idx, int N,
                 int qstride, const int32_t* __restrict__ kept_offsets,
                 const float* __restrict__ Kh, const float* __restrict__ Vh,
                 const int32_t* __restrict__ passage_offsets,
                 const int32_t* __restrict__ query_passages,
-                const uint64_t* __restrict__ rowmask, int H, int total_kept,
-                int total_passages, int total_tokens, int k_max, int P_max, float sm_scale,
-                float* __restrict__ O, float* __restrict__ lse) {
-  constexpr int E = D / 64;            // features per lane
-  __shared__ float qs[4][D];
-  __shared__ float ps[4][64];
-  const int b = blockIdx.y;
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+                const uint64_t* __restrict__ rowmask, int H, int groups, int tiles,
+                int total_kept, int total_passages, int total_tokens, int k_max, int P_max,
+                float scale_log2, float* __restrict__ O, float* __restrict__ lse) {
+  constexpr int NQ = D / 16;           // 16-feature groups of K . Q^T
+  constexpr int NH = D / 64;           // 64-feature halves of O
+  constexpr int OS = D + 4;            // floats per row of a wave's partial (bank spread)
+  __shared__ __align__(16) float po[NW][kF32Rows][OS];
+  __shared__ float pm[NW][kF32Rows], pl[NW][kF32Rows];
+  // all row tiles of a (question, head) on one XCD (workgroup id L goes to
+  // XCD L % 8), where they share its K and V in the L2
+  const int L = blockIdx.x, grp = (L & 7) + 8 * ((L >> 3) / tiles);
+  if (grp >= groups) return;
+  const int b = grp / H, h = grp % H, r0 = ((L >> 3) % tiles) * kF32Rows;
   int k0, k1, p0, p1;
   range_of(kept_offsets, b, total_kept, k0, k1);
   range_of(query_passages, b, total_passages, p0, p1);
   const int kq = min(k1 - k0, k_max);
   const int P = min(min(p1 - p0, P_max), 64);
-  const int item = blockIdx.x * 4 + wave;
-  const int r = item / H, h = item % H;
-  if (r >= kq) return;                  // whole wave; no block barrier below
+  if (r0 >= kq) return;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, r16 = lane & 15;
 
-  const float* qrow;
-  if (kept_idx) {
-    const int src = clampi(kept_idx[k0 + r], 0, N - 1);
-    qrow = qbase + ((size_t)b * N + src) * qstride + (size_t)h * D;
-  } else {
-    qrow = qbase + (size_t)(k0 + r) * qstride + (size_t)h * D;
-  }
+  // this lane's row (a lane past the question's rows repeats its last one,
+  // adjacent to nothing)
+  const int r = min(r0 + r16, kq - 1);
+  uint64_t mk = (r0 + r16 < kq) ? rowmask[k0 + r] : 0ull;
+  if (P < 64) mk &= (1ull << P) - 1ull;
+  const float* qrow = kept_idx
+      ? qbase + ((size_t)b * N + clampi(kept_idx[k0 + r], 0, N - 1)) * qstride + (size_t)h * D
+      : qbase + (size_t)(k0 + r) * qstride + (size_t)h * D;
+  f32x4_t qf[NQ];
 #pragma unroll
-  for (int e = 0; e < E; ++e) qs[wave][lane * E + e] = qrow[lane * E + e];
-  __builtin_amdgcn_wave_barrier();
+  for (int q = 0; q < NQ; ++q) qf[q] = *reinterpret_cast<const f32x4_t*>(qrow + 16 * q + 4 * g);
+  uint64_t U = mk;                     // passages adjacent to some row of the tile
+#pragma unroll
+  for (int x = 1; x < 16; x <<= 1) U |= (uint64_t)__shfl_xor((unsigned long long)U, x, kWave);
+  U = uniform64(U);
 
-  uint64_t m = rowmask[k0 + r];
-  if (P < 64) m &= (1ull << P) - 1ull;
-  float m_run = -INFINITY, l_run = 0.f;
-  float o[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) o[e] = 0.f;
-  while (m) {
-    const int j = __builtin_ctzll(m);
-    m &= m - 1ull;
-    int ts, te;
-    range_of(passage_offsets, p0 + j, total_tokens, ts, te);
-    for (int t0 = ts; t0 < te; t0 += 64) {
-      const int t = t0 + lane;
-      float x = -INFINITY;
-      if (t < te) {
-        const float* krow = Kh + ((size_t)t * H + h) * D;
-        float s = 0.f;
-        for (int c = 0; c < D; ++c) s = fmaf(qs[wave][c], krow[c], s);
-        x = s * sm_scale;
-      }
-      const float m_new = fmaxf(m_run, wave_max_f32(x));
-      const float alpha = (m_run == -INFINITY) ? 0.f : expf(m_run - m_new);
-      const float p = (x == -INFINITY) ? 0.f : expf(x - m_new);
-      l_run = l_run * alpha + wave_sum_f32(p);
-      m_run = m_new;
-      ps[wave][lane] = p;
-      __builtin_amdgcn_wave_barrier();
-      const int n = min(64, te - t0);
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        float a = o[e] * alpha;
-        for (int q = 0; q < n; ++q)
-          a = fmaf(ps[wave][q], Vh[((size_t)(t0 + q) * H + h) * D + lane * E + e], a);
-        o[e] = a;
-      }
-      __builtin_amdgcn_wave_barrier();
+  // A block in flight: its K and V operands, passage and tokens t .. te - 1.
+  struct Block {
+    f32x4_t k[NQ], v[4 * NH];
+    int j, t, te;
+  };
+  // the wave's cursor: block nb of passage j (nbk blocks, tokens ts .. te - 1)
+  uint64_t rem = U;
+  int j = 0, ts = 0, te = 0, nb = wave, nbk = 0;
+  auto load = [&](Block& x) -> bool {    // the next block of the wave, if any
+    while (nb >= nbk) {
+      if (!rem) return false;
+      nb -= nbk;
+      j = __builtin_ctzll(rem);
+      rem &= rem - 1ull;
+      range_of(passage_offsets, p0 + j, total_tokens, ts, te);
+      ts = __builtin_amdgcn_readfirstlane(ts);
+      te = __builtin_amdgcn_readfirstlane(te);
+      nbk = (te - ts + 15) / 16;
     }
-  }
-  const float inv = (l_run > 0.f) ? 1.f / l_run : 0.f;
-  float* orow = O + ((size_t)(k0 + r) * H + h) * D;
+    x.j = j;
+    x.t = ts + 16 * nb;
+    x.te = te;
+    nb += NW;
+    // tokens past the passage's end read its last one (masked below)
+    const float* kr = Kh + ((size_t)min(x.t + r16, te - 1) * H + h) * D + 4 * g;
 #pragma unroll
-  for (int e = 0; e < E; ++e) orow[lane * E + e] = o[e] * inv;
-  if (lse && lane == 0)
-    lse[(size_t)(k0 + r) * H + h] = (l_run > 0.f) ? m_run + logf(l_run) : -INFINITY;
+    for (int q = 0; q < NQ; ++q) x.k[q] = *reinterpret_cast<const f32x4_t*>(kr + 16 * q);
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      const float* vr = Vh + ((size_t)min(x.t + 4 * g + jj, te - 1) * H + h) * D + 4 * r16;
+#pragma unroll
+      for (int hf = 0; hf < NH; ++hf)
+        x.v[NH * jj + hf] = *reinterpret_cast<const f32x4_t*>(vr + 64 * hf);
+    }
+    return true;
+  };
+
+  f32x4_t acc[4 * NH];                 // block e of half hf: features 64hf + 16g + 4i + e
+#pragma unroll
+  for (int e = 0; e < 4 * NH; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  float m_run = -INFINITY, l_run = 0.f;   // l_run: this lane's share of the row's sum
+  auto compute = [&](const Block& x) {
+    f32x4_t s2[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        s2[q & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.k[q][m], qf[q][m], s2[q & 1], 0, 0, 0);
+    const bool adj = (mk >> x.j) & 1ull;
+    float s[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      s[i] = (adj && x.t + 4 * g + i < x.te) ? (s2[0][i] + s2[1][i]) * scale_log2 : -INFINITY;
+    // the reference maximum moves when a logit exceeds it by more than kLazy
+    // (weights stay <= 2^kLazy), so most blocks need no exchange or rescale
+    const float lm = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+    if (__any(lm > m_run + kLazy)) {
+      float mx = fmaxf(lm, swap16(lm));
+      mx = fmaxf(mx, swap_halves(mx));
+      if (mx > m_run + kLazy) {
+        const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - mx);
+        m_run = mx;
+        l_run *= alpha;
+#pragma unroll
+        for (int e = 0; e < 4 * NH; ++e) acc[e] *= alpha;
+      }
+    }
+    const float ref = m_run == -INFINITY ? 0.f : m_run;   // (no logit of the row yet: weights 0)
+    float p[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(s[i] - ref);
+    l_run += (p[0] + p[1]) + (p[2] + p[3]);
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+      for (int e = 0; e < 4 * NH; ++e)
+        acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.v[NH * jj + (e >> 2)][e & 3], p[jj],
+                                                      acc[e], 0, 0, 0);
+  };
+  // two blocks in turn: one's loads are in flight while the other computes
+  Block xa, xb;
+  bool more = load(xa);
+  while (more) {
+    const bool second = load(xb);
+    compute(xa);
+    if (!second) break;
+    more = load(xa);
+    compute(xb);
+  }
+
+  // the waves' partials, merged in wave order
+  float l_tot = l_run + swap16(l_run);
+  l_tot += swap_halves(l_tot);
+  if (g == 0) {
+    pm[wave][r16] = m_run;
+    pl[wave][r16] = l_tot;
+  }
+#pragma unroll
+  for (int hf = 0; hf < NH; ++hf)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      *reinterpret_cast<f32x4_t*>(&po[wave][r16][64 * hf + 16 * g + 4 * i]) =
+          f32x4_t{acc[4 * hf][i], acc[4 * hf + 1][i], acc[4 * hf + 2][i], acc[4 * hf + 3][i]};
+  __syncthreads();
+  for (int u = threadIdx.x; u < kF32Rows * (D / 4); u += 64 * NW) {
+    const int ri = u / (D / 4), c = 4 * (u % (D / 4));
+    if (r0 + ri >= kq) continue;
+    float M = pm[0][ri];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, pm[w][ri]);
+    const float ref = M == -INFINITY ? 0.f : M;
+    f32x4_t o = {0.f, 0.f, 0.f, 0.f};
+    float l = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float a = __builtin_amdgcn_exp2f(pm[w][ri] - ref);
+      l = fmaf(pl[w][ri], a, l);
+      o += *reinterpret_cast<const f32x4_t*>(&po[w][ri][c]) * a;
+    }
+    const float inv = (l > 0.f) ? 1.f / l : 0.f;
+    const size_t row = (size_t)(k0 + r0 + ri);
+    *reinterpret_cast<f32x4_t*>(O + (row * H + h) * D + c) = o * inv;
+    if (lse && c == 0) lse[row * H + h] = (l > 0.f) ? (M + log2f(l)) * kLn2 : -INFINITY;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -772,15 +890,21 @@ hipError_t launch_attention(const skip_problem_t& p, QuerySource q,
     else SKIP_ATTN_SPARSE(128);
 #undef SKIP_ATTN_SPARSE
   } else {
-    dim3 grid((p.k_max * p.H + 3) / 4, p.B);
-#define SKIP_ATTN_F32(DD)                                                                    \
-  hipLaunchKernelGGL(attn_f32_kernel<DD>, grid, dim3(256), 0, s, (const float*)q.base,       \
-                     q.kept_idx, q.N, qstride, kept_offsets, (const float*)Kh,               \
-                     (const float*)Vh, passage_offsets, query_passages, rowmask, p.H,        \
-                     p.total_kept, p.total_passages, p.total_tokens, p.k_max, p.P_max,       \
-                     p.sm_scale, (float*)O, lse)
-    if (p.d_h == 64) SKIP_ATTN_F32(64);
-    else SKIP_ATTN_F32(128);
+    const long long groups = (long long)p.B * p.H;
+    const int tiles = (p.k_max + kF32Rows - 1) / kF32Rows;
+    const long long nwg = 8 * ((groups + 7) / 8) * tiles;
+    if (nwg > INT32_MAX / 512) return hipErrorInvalidValue;
+#define SKIP_ATTN_F32(DD, NW)                                                                \
+  hipLaunchKernelGGL((attn_f32_kernel<DD, NW>), dim3((unsigned)nwg), dim3(64 * NW), 0, s,    \
+                     (const float*)q.base, q.kept_idx, q.N, qstride, kept_offsets,           \
+                     (const float*)Kh, (const float*)Vh, passage_offsets, query_passages,    \
+                     rowmask, p.H, (int)groups, tiles, p.total_kept, p.total_passages,       \
+                     p.total_tokens, p.k_max, p.P_max, p.sm_scale * kLog2e, (float*)O, lse)
+    const int nw = nwg >= kF32Wide ? 4 : 8;
+    if (p.d_h == 64 && nw == 4) SKIP_ATTN_F32(64, 4);
+    else if (p.d_h == 64) SKIP_ATTN_F32(64, 8);
+    else if (nw == 4) SKIP_ATTN_F32(128, 4);
+    else SKIP_ATTN_F32(128, 8);
 #undef SKIP_ATTN_F32
   }
   return hipGetLastError();
