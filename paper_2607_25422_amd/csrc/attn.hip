@@ -8,8 +8,8 @@
 // bf16 path (MFMA): passage-major, only the graph's edges are computed (the
 // kernel comment below); a device-built work list orders the items by cost.
 //
-// fp32 path: 16 rows per workgroup on the float32 matrix cores (at its
-// kernel).
+// fp32 inputs and small bf16 problems: 16 rows per workgroup, token blocks
+// split over its waves (at that kernel).
 #include "skip_common.h"
 #include "skip_internal.h"
 #include "skip_plan.h"
@@ -645,55 +645,191 @@ attn_plan_kernel(const int32_t* __restrict__ kept_offsets,
 }
 
 // ---------------------------------------------------------------------------
-// fp32 path on the float32 matrix cores (v_mfma_f32_16x16x4_f32: float32
-// products and sums).  Workgroup = (question, head, 16 consecutive kept rows)
-// of NW waves, which take the 16-token blocks of the passages adjacent to at
-// least one of the rows in turn (block i to wave i mod NW), each with its own
-// (O, max, sum); they are merged in wave order through LDS at the end, so the
-// loop has no barrier and no LDS access.  Per block:
-//   S^T (16 tokens x 16 rows) = K . Q^T, a logit of a row not adjacent to the
+// Row-tile path (fp32 inputs, and small bf16 problems).  Workgroup =
+// (question, head, 16 consecutive kept rows) of NW waves, which take the
+// token blocks of the passages adjacent to at least one of the rows in turn
+// (block i to wave i mod NW), each with its own (O, max, sum); they are
+// merged in wave order through LDS at the end, so the loop has no barrier and
+// no LDS access.  Per block:
+//   S^T (tokens x 16 rows) = K . Q^T, a logit of a row not adjacent to the
 //   passage at -inf, online softmax in base 2, O^T += V^T . P^T.
-// Both products take their operands as 16-byte loads, in the order the lanes
-// hold them: lane l (r16 = l % 16, g = l / 16) supplies contraction slot g,
-// and which feature (S) or token (O) a slot stands for is free as long as
-// both operands agree.  S: slot g of product m of a 16-feature group is
-// feature 4g + m (one float4 of the row).  O: slot g of product j is token
-// 4g + j of the block, where S^T leaves that logit, and output row f of
-// feature block e is feature 4f + e (one float4 of a token's 64 features), so
-// a lane ends with 16 consecutive features of its row.
+// Both products take their operands as loaded, in the order the lanes hold
+// them: lane l (r16 = l % 16, g = l / 16) supplies the contraction slots of
+// group g, and which feature (S) or token (O) a slot stands for is free as
+// long as both operands agree.
+template <typename T, int D> struct TileOps;
+
+// float32: 16 tokens a block, v_mfma_f32_16x16x4_f32 (float32 products and
+// sums).  S: slot g of product m of a 16-feature group is feature 4g + m (one
+// float4 of the row).  O: slot g of product j is token 4g + j of the block,
+// where S^T leaves that logit, and output row f of feature block e is feature
+// 4f + e (one float4 of a token's 64 features).
+template <int D> struct TileOps<float, D> {
+  static constexpr int kTok = 16;      // tokens per block
+  static constexpr int kS = 4;         // logits per lane and block
+  static constexpr int NQ = D / 16, NH = D / 64;
+  static constexpr int NA = D / 16;    // accumulator blocks (16 features x 16 rows)
+  struct Q { f32x4_t x[NQ]; };
+  struct KV { f32x4_t k[NQ], v[4 * NH]; };
+  __device__ static void load_q(Q& q, const float* row, int g) {
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) q.x[i] = *reinterpret_cast<const f32x4_t*>(row + 16 * i + 4 * g);
+  }
+  // token of logit i in the block
+  __device__ static int token(int g, int i) { return 4 * g + i; }
+  // head h's tokens t .. of a passage ending at te (past it: the last token,
+  // masked in the softmax)
+  __device__ static void load_kv(KV& x, const float* Kh, const float* Vh, int t, int te,
+                                 size_t stride, int g, int r16) {
+    const float* kr = Kh + (size_t)min(t + r16, te - 1) * stride + 4 * g;
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) x.k[i] = *reinterpret_cast<const f32x4_t*>(kr + 16 * i);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float* vr = Vh + (size_t)min(t + 4 * g + j, te - 1) * stride + 4 * r16;
+#pragma unroll
+      for (int hf = 0; hf < NH; ++hf)
+        x.v[NH * j + hf] = *reinterpret_cast<const f32x4_t*>(vr + 64 * hf);
+    }
+  }
+  __device__ static void logits(float (&s)[kS], const Q& q, const KV& x) {
+    f32x4_t a[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int i = 0; i < NQ; ++i)
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        a[i & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.k[i][m], q.x[i][m], a[i & 1], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s[i] = a[0][i] + a[1][i];
+  }
+  __device__ static void weigh(f32x4_t (&acc)[NA], const KV& x, const float (&p)[kS]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < NA; ++e)
+        acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.v[NH * j + (e >> 2)][e & 3], p[j],
+                                                      acc[e], 0, 0, 0);
+  }
+  // four consecutive features from element i of the accumulators: q-th piece
+  // of the lane's 16 NH features, starting at feature first(g, q)
+  static constexpr int kPieces = 4 * NH;
+  __device__ static int first(int g, int q) { return 64 * (q >> 2) + 16 * g + 4 * (q & 3); }
+  __device__ static f32x4_t piece(const f32x4_t (&acc)[NA], int q) {
+    const int hf = q >> 2, i = q & 3;
+    return f32x4_t{acc[4 * hf][i], acc[4 * hf + 1][i], acc[4 * hf + 2][i], acc[4 * hf + 3][i]};
+  }
+};
+
+// bfloat16: 32 tokens a block, v_mfma_f32_16x16x32_bf16.  S as in the sparse
+// kernel.  O: a lane loads E = D / 16 features of each of its eight tokens and
+// pairs tokens into the slots' order (one v_perm_b32 per word), so output row
+// f of feature block e is feature E f + e; the weights as bf16 pairs hi + lo.
+template <int D> struct TileOps<bf16_t, D> {
+  static constexpr int kTok = 32, kS = 8;
+  static constexpr int KB = D / 32;
+  static constexpr int NA = D / 16, E = D / 16;      // E: features per lane of a token
+  typedef uint32_t vword __attribute__((ext_vector_type(E / 2)));
+  struct Q { u32x4 x[KB]; };
+  struct KV { u32x4 k[2][KB]; vword v[8]; };
+  __device__ static void load_q(Q& q, const bf16_t* row, int g) {
+#pragma unroll
+    for (int i = 0; i < KB; ++i) q.x[i] = *reinterpret_cast<const u32x4*>(row + 32 * i + 8 * g);
+  }
+  __device__ static int token(int g, int i) { return 16 * (i >> 2) + 4 * g + (i & 3); }
+  __device__ static void load_kv(KV& x, const bf16_t* Kh, const bf16_t* Vh, int t, int te,
+                                 size_t stride, int g, int r16) {
+#pragma unroll
+    for (int th = 0; th < 2; ++th) {
+      const bf16_t* kr = Kh + (size_t)min(t + 16 * th + r16, te - 1) * stride + 8 * g;
+#pragma unroll
+      for (int i = 0; i < KB; ++i) x.k[th][i] = *reinterpret_cast<const u32x4*>(kr + 32 * i);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      x.v[i] = *reinterpret_cast<const vword*>(
+          Vh + (size_t)min(t + token(g, i), te - 1) * stride + E * r16);
+  }
+  __device__ static void logits(float (&s)[kS], const Q& q, const KV& x) {
+#pragma unroll
+    for (int th = 0; th < 2; ++th) {
+      f32x4_t a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < KB; ++i) a = mfma16_bf16(x.k[th][i], q.x[i], a);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[4 * th + i] = a[i];
+    }
+  }
+  __device__ static void weigh(f32x4_t (&acc)[NA], const KV& x, const float (&p)[kS]) {
+    u32x4 hi, lo;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t b0 = __float_as_uint(p[2 * q]), b1 = __float_as_uint(p[2 * q + 1]);
+      hi[q] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
+      lo[q] = pack2_bf16(p[2 * q] - __uint_as_float(b0 & 0xffff0000u),
+                         p[2 * q + 1] - __uint_as_float(b1 & 0xffff0000u));
+    }
+#pragma unroll
+    for (int e = 0; e < NA; ++e) {
+      u32x4 a;                          // feature E f + e of the eight tokens
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        a[q] = __builtin_amdgcn_perm(x.v[2 * q + 1][e >> 1], x.v[2 * q][e >> 1],
+                                     (e & 1) ? 0x07060302u : 0x05040100u);
+      acc[e] = mfma16_bf16(a, hi, acc[e]);
+      acc[e] = mfma16_bf16(a, lo, acc[e]);
+    }
+  }
+  static constexpr int kPieces = E;
+  __device__ static int first(int g, int q) { return 4 * E * g + 4 * q; }
+  __device__ static f32x4_t piece(const f32x4_t (&acc)[NA], int q) {
+    const int i = 4 * q / E, e = 4 * q % E;
+    return f32x4_t{acc[e][i], acc[e + 1][i], acc[e + 2][i], acc[e + 3][i]};
+  }
+};
+
 // Bound by the matrix cores at large batches (rows not adjacent to a passage
 // of their tile compute for nothing there; one wave per row and head, edges
 // only, on the vector units spent ten times as long) and by the wave's load
 // and product chain at small ones.  Measured against that form: 8 questions
 // of 96 rows, 16 heads of 64, 5 passages of 97-160 tokens 35.5 us (359); one
 // question of 96 rows, 4 heads of 64, 4 passages of 64 tokens 7.9 us (38.3).
-constexpr int kF32Rows = 16;
+constexpr int kTileRows = 16;
 // Workgroups from which four waves each fill the chip; below, eight shorten
 // the wave's chain (routes of 350 to 2304 workgroups: 134 us with four and
 // 111 with eight at the low end, equal within 1.5 % at 768, 154 with eight
 // and 140 with four at the high end).
-constexpr long long kF32Wide = 1024;
+constexpr long long kTileWide = 1024;
+// bf16 problems of at most this many workgroups x d_h go by row tiles, larger
+// ones to the sparse kernel, whose items of up to 192 rows read K and V once
+// but leave most of the chip idle at few (question, head) pairs and walk the
+// passages one tile of tokens after the other.  Routes, tiles against sparse
+// (5 x 128, 10 x 256 and 20 x 256 tokens, 48 to 384 rows): at 768 workgroups
+// of d_h = 64 59-145 us against 66-163, at 1536 75-230 against 77-167; at 384
+// of d_h = 128 68-184 against 88-192, at 768 84-226 against 80-205; one
+// question of 96 rows, 16 heads of 64: 44 against 59, 64 against 102 and 82
+// against 155.
+constexpr long long kTileWork = 768 * 64;
 
-template <int D, int NW>
-__global__ void __launch_bounds__(64 * NW)
-attn_f32_kernel(const float* __restrict__ qbase, const int32_t* __restrict__ kept_idx, int N,
-                int qstride, const int32_t* __restrict__ kept_offsets,
-                const float* __restrict__ Kh, const float* __restrict__ Vh,
-                const int32_t* __restrict__ passage_offsets,
-                const int32_t* __restrict__ query_passages,
-                const uint64_t* __restrict__ rowmask, int H, int groups, int tiles,
-                int total_kept, int total_passages, int total_tokens, int k_max, int P_max,
-                float scale_log2, float* __restrict__ O, float* __restrict__ lse) {
-  constexpr int NQ = D / 16;           // 16-feature groups of K . Q^T
-  constexpr int NH = D / 64;           // 64-feature halves of O
+template <typename T, int D, int NW>
+__global__ void __launch_bounds__(64 * NW, 2)
+attn_tile_kernel(const T* __restrict__ qbase, const int32_t* __restrict__ kept_idx, int N,
+                 int qstride, const int32_t* __restrict__ kept_offsets,
+                 const T* __restrict__ Kh, const T* __restrict__ Vh,
+                 const int32_t* __restrict__ passage_offsets,
+                 const int32_t* __restrict__ query_passages,
+                 const uint64_t* __restrict__ rowmask, int H, int groups, int tiles,
+                 int total_kept, int total_passages, int total_tokens, int k_max, int P_max,
+                 float scale_log2, void* __restrict__ O, int o_f32, float* __restrict__ lse) {
+  using Ops = TileOps<T, D>;
+  constexpr int TB = Ops::kTok, NS = Ops::kS, NA = Ops::NA;
   constexpr int OS = D + 4;            // floats per row of a wave's partial (bank spread)
-  __shared__ __align__(16) float po[NW][kF32Rows][OS];
-  __shared__ float pm[NW][kF32Rows], pl[NW][kF32Rows];
+  __shared__ __align__(16) float po[NW][kTileRows][OS];
+  __shared__ float pm[NW][kTileRows], pl[NW][kTileRows];
   // all row tiles of a (question, head) on one XCD (workgroup id L goes to
   // XCD L % 8), where they share its K and V in the L2
   const int L = blockIdx.x, grp = (L & 7) + 8 * ((L >> 3) / tiles);
   if (grp >= groups) return;
-  const int b = grp / H, h = grp % H, r0 = ((L >> 3) % tiles) * kF32Rows;
+  const int b = grp / H, h = grp % H, r0 = ((L >> 3) % tiles) * kTileRows;
   int k0, k1, p0, p1;
   range_of(kept_offsets, b, total_kept, k0, k1);
   range_of(query_passages, b, total_passages, p0, p1);
@@ -709,12 +845,10 @@ attn_f32_kernel(const float* __restrict__ qbase, const int32_t* __restrict__ kep
   const int r = min(r0 + r16, kq - 1);
   uint64_t mk = (r0 + r16 < kq) ? rowmask[k0 + r] : 0ull;
   if (P < 64) mk &= (1ull << P) - 1ull;
-  const float* qrow = kept_idx
+  typename Ops::Q qf;
+  Ops::load_q(qf, kept_idx
       ? qbase + ((size_t)b * N + clampi(kept_idx[k0 + r], 0, N - 1)) * qstride + (size_t)h * D
-      : qbase + (size_t)(k0 + r) * qstride + (size_t)h * D;
-  f32x4_t qf[NQ];
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) qf[q] = *reinterpret_cast<const f32x4_t*>(qrow + 16 * q + 4 * g);
+      : qbase + (size_t)(k0 + r) * qstride + (size_t)h * D, g);
   uint64_t U = mk;                     // passages adjacent to some row of the tile
 #pragma unroll
   for (int x = 1; x < 16; x <<= 1) U |= (uint64_t)__shfl_xor((unsigned long long)U, x, kWave);
@@ -722,7 +856,7 @@ attn_f32_kernel(const float* __restrict__ qbase, const int32_t* __restrict__ kep
 
   // A block in flight: its K and V operands, passage and tokens t .. te - 1.
   struct Block {
-    f32x4_t k[NQ], v[4 * NH];
+    typename Ops::KV kv;
     int j, t, te;
   };
   // the wave's cursor: block nb of passage j (nbk blocks, tokens ts .. te - 1)
@@ -737,45 +871,32 @@ attn_f32_kernel(const float* __restrict__ qbase, const int32_t* __restrict__ kep
       range_of(passage_offsets, p0 + j, total_tokens, ts, te);
       ts = __builtin_amdgcn_readfirstlane(ts);
       te = __builtin_amdgcn_readfirstlane(te);
-      nbk = (te - ts + 15) / 16;
+      nbk = (te - ts + TB - 1) / TB;
     }
     x.j = j;
-    x.t = ts + 16 * nb;
+    x.t = ts + TB * nb;
     x.te = te;
     nb += NW;
-    // tokens past the passage's end read its last one (masked below)
-    const float* kr = Kh + ((size_t)min(x.t + r16, te - 1) * H + h) * D + 4 * g;
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) x.k[q] = *reinterpret_cast<const f32x4_t*>(kr + 16 * q);
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-      const float* vr = Vh + ((size_t)min(x.t + 4 * g + jj, te - 1) * H + h) * D + 4 * r16;
-#pragma unroll
-      for (int hf = 0; hf < NH; ++hf)
-        x.v[NH * jj + hf] = *reinterpret_cast<const f32x4_t*>(vr + 64 * hf);
-    }
+    Ops::load_kv(x.kv, Kh + (size_t)h * D, Vh + (size_t)h * D, x.t, te, (size_t)H * D, g, r16);
     return true;
   };
 
-  f32x4_t acc[4 * NH];                 // block e of half hf: features 64hf + 16g + 4i + e
+  f32x4_t acc[NA];
 #pragma unroll
-  for (int e = 0; e < 4 * NH; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int e = 0; e < NA; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.f;   // l_run: this lane's share of the row's sum
   auto compute = [&](const Block& x) {
-    f32x4_t s2[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-    for (int q = 0; q < NQ; ++q)
-#pragma unroll
-      for (int m = 0; m < 4; ++m)
-        s2[q & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.k[q][m], qf[q][m], s2[q & 1], 0, 0, 0);
+    float s[NS];
+    Ops::logits(s, qf, x.kv);
     const bool adj = (mk >> x.j) & 1ull;
-    float s[4];
+    float lm = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      s[i] = (adj && x.t + 4 * g + i < x.te) ? (s2[0][i] + s2[1][i]) * scale_log2 : -INFINITY;
+    for (int i = 0; i < NS; ++i) {
+      s[i] = (adj && x.t + Ops::token(g, i) < x.te) ? s[i] * scale_log2 : -INFINITY;
+      lm = fmaxf(lm, s[i]);
+    }
     // the reference maximum moves when a logit exceeds it by more than kLazy
     // (weights stay <= 2^kLazy), so most blocks need no exchange or rescale
-    const float lm = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
     if (__any(lm > m_run + kLazy)) {
       float mx = fmaxf(lm, swap16(lm));
       mx = fmaxf(mx, swap_halves(mx));
@@ -784,20 +905,18 @@ attn_f32_kernel(const float* __restrict__ qbase, const int32_t* __restrict__ kep
         m_run = mx;
         l_run *= alpha;
 #pragma unroll
-        for (int e = 0; e < 4 * NH; ++e) acc[e] *= alpha;
+        for (int e = 0; e < NA; ++e) acc[e] *= alpha;
       }
     }
     const float ref = m_run == -INFINITY ? 0.f : m_run;   // (no logit of the row yet: weights 0)
-    float p[4];
+    float p[NS], ls = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(s[i] - ref);
-    l_run += (p[0] + p[1]) + (p[2] + p[3]);
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-      for (int e = 0; e < 4 * NH; ++e)
-        acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.v[NH * jj + (e >> 2)][e & 3], p[jj],
-                                                      acc[e], 0, 0, 0);
+    for (int i = 0; i < NS; ++i) {
+      p[i] = __builtin_amdgcn_exp2f(s[i] - ref);
+      ls += p[i];
+    }
+    l_run += ls;
+    Ops::weigh(acc, x.kv, p);
   };
   // two blocks in turn: one's loads are in flight while the other computes
   Block xa, xb;
@@ -818,13 +937,10 @@ attn_f32_kernel(const float* __restrict__ qbase, const int32_t* __restrict__ kep
     pl[wave][r16] = l_tot;
   }
 #pragma unroll
-  for (int hf = 0; hf < NH; ++hf)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      *reinterpret_cast<f32x4_t*>(&po[wave][r16][64 * hf + 16 * g + 4 * i]) =
-          f32x4_t{acc[4 * hf][i], acc[4 * hf + 1][i], acc[4 * hf + 2][i], acc[4 * hf + 3][i]};
+  for (int q = 0; q < Ops::kPieces; ++q)
+    *reinterpret_cast<f32x4_t*>(&po[wave][r16][Ops::first(g, q)]) = Ops::piece(acc, q);
   __syncthreads();
-  for (int u = threadIdx.x; u < kF32Rows * (D / 4); u += 64 * NW) {
+  for (int u = threadIdx.x; u < kTileRows * (D / 4); u += 64 * NW) {
     const int ri = u / (D / 4), c = 4 * (u % (D / 4));
     if (r0 + ri >= kq) continue;
     float M = pm[0][ri];
@@ -841,12 +957,24 @@ attn_f32_kernel(const float* __restrict__ qbase, const int32_t* __restrict__ kep
     }
     const float inv = (l > 0.f) ? 1.f / l : 0.f;
     const size_t row = (size_t)(k0 + r0 + ri);
-    *reinterpret_cast<f32x4_t*>(O + (row * H + h) * D + c) = o * inv;
+    const size_t off = (row * H + h) * D + c;
+    o *= inv;
+    if (o_f32)
+      *reinterpret_cast<f32x4_t*>(static_cast<float*>(O) + off) = o;
+    else
+      *reinterpret_cast<uint2*>(static_cast<bf16_t*>(O) + off) =
+          make_uint2(pack2_bf16(o[0], o[1]), pack2_bf16(o[2], o[3]));
     if (lse && c == 0) lse[row * H + h] = (l > 0.f) ? (M + log2f(l)) * kLn2 : -INFINITY;
   }
 }
 
 // ---------------------------------------------------------------------------
+// Whether the row-tile kernel runs (else the passage-major sparse kernel).
+bool attn_by_tiles(const skip_problem_t& p) {
+  if (p.dtype != SKIP_BF16) return true;
+  return (long long)p.B * p.H * ((p.k_max + kTileRows - 1) / kTileRows) * p.d_h <= kTileWork;
+}
+
 long long attn_plan_ids(const skip_problem_t& p) {
   if (p.dtype != SKIP_BF16 || p.k_max <= 0 || p.B <= 0 || p.H <= 0) return 0;
   const long long runs = ((long long)p.B * p.H + 7) / 8;
@@ -858,7 +986,7 @@ hipError_t launch_attention_plan(const skip_problem_t& p, const int32_t* kept_of
                                  const int32_t* query_passages,
                                  const int32_t* passage_offsets, int32_t* plan, hipStream_t s) {
   const long long n_ids = attn_plan_ids(p);
-  if (n_ids == 0) return hipSuccess;
+  if (n_ids == 0 || attn_by_tiles(p)) return hipSuccess;
   if (n_ids > INT32_MAX / 16 || (long long)p.B * p.H > INT32_MAX / 16)
     return hipErrorInvalidValue;
   hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, kept_offsets,
@@ -875,7 +1003,7 @@ hipError_t launch_attention(const skip_problem_t& p, QuerySource q,
                             hipStream_t s) {
   if (p.k_max <= 0) return hipSuccess;
   const int qstride = p.d;
-  if (p.dtype == SKIP_BF16) {
+  if (!attn_by_tiles(p)) {
     const long long n_ids = attn_plan_ids(p);
     if (n_ids > INT32_MAX / 16 || (long long)p.B * p.H > INT32_MAX / 16)
       return hipErrorInvalidValue;
@@ -891,21 +1019,28 @@ hipError_t launch_attention(const skip_problem_t& p, QuerySource q,
 #undef SKIP_ATTN_SPARSE
   } else {
     const long long groups = (long long)p.B * p.H;
-    const int tiles = (p.k_max + kF32Rows - 1) / kF32Rows;
+    const int tiles = (p.k_max + kTileRows - 1) / kTileRows;
     const long long nwg = 8 * ((groups + 7) / 8) * tiles;
     if (nwg > INT32_MAX / 512) return hipErrorInvalidValue;
-#define SKIP_ATTN_F32(DD, NW)                                                                \
-  hipLaunchKernelGGL((attn_f32_kernel<DD, NW>), dim3((unsigned)nwg), dim3(64 * NW), 0, s,    \
-                     (const float*)q.base, q.kept_idx, q.N, qstride, kept_offsets,           \
-                     (const float*)Kh, (const float*)Vh, passage_offsets, query_passages,    \
-                     rowmask, p.H, (int)groups, tiles, p.total_kept, p.total_passages,       \
-                     p.total_tokens, p.k_max, p.P_max, p.sm_scale * kLog2e, (float*)O, lse)
-    const int nw = nwg >= kF32Wide ? 4 : 8;
-    if (p.d_h == 64 && nw == 4) SKIP_ATTN_F32(64, 4);
-    else if (p.d_h == 64) SKIP_ATTN_F32(64, 8);
-    else if (nw == 4) SKIP_ATTN_F32(128, 4);
-    else SKIP_ATTN_F32(128, 8);
-#undef SKIP_ATTN_F32
+#define SKIP_ATTN_TILE(T, DD, NW)                                                            \
+  hipLaunchKernelGGL((attn_tile_kernel<T, DD, NW>), dim3((unsigned)nwg), dim3(64 * NW), 0,   \
+                     s, (const T*)q.base, q.kept_idx, q.N, qstride, kept_offsets,            \
+                     (const T*)Kh, (const T*)Vh, passage_offsets, query_passages, rowmask,   \
+                     p.H, (int)groups, tiles, p.total_kept, p.total_passages,                \
+                     p.total_tokens, p.k_max, p.P_max, p.sm_scale * kLog2e, O,               \
+                     p.dtype == SKIP_F32 || p.o_f32, lse)
+    const bool wide = nwg >= kTileWide;
+    if (p.dtype == SKIP_BF16) {
+      if (p.d_h == 64) SKIP_ATTN_TILE(bf16_t, 64, 8);
+      else SKIP_ATTN_TILE(bf16_t, 128, 8);
+    } else if (p.d_h == 64) {
+      if (wide) SKIP_ATTN_TILE(float, 64, 4);
+      else SKIP_ATTN_TILE(float, 64, 8);
+    } else {
+      if (wide) SKIP_ATTN_TILE(float, 128, 4);
+      else SKIP_ATTN_TILE(float, 128, 8);
+    }
+#undef SKIP_ATTN_TILE
   }
   return hipGetLastError();
 }

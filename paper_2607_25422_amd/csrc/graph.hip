@@ -537,7 +537,7 @@ hipError_t launch_edge_select(const skip_problem_t& p, EdgePartials ep,
                               hipStream_t s, const uint8_t* passage_keep,
                               const int32_t* passage_offsets, int32_t* plan) {
   PlanArgs pa{};
-  const long long n_ids = plan ? attn_plan_ids(p) : 0;
+  const long long n_ids = plan && !attn_by_tiles(p) ? attn_plan_ids(p) : 0;
   if (n_ids > INT32_MAX / 16) return hipErrorInvalidValue;
   if (n_ids > 0) {
     pa.items = reinterpret_cast<int4*>(plan);

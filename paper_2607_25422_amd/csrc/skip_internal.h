@@ -140,6 +140,8 @@ hipError_t launch_csr_to_mask(const skip_problem_t& p, const int32_t* kept_offse
 // Workgroup ids of the bf16 attention launch (0 for fp32): the work list
 // takes one 16-byte record per id.
 long long attn_plan_ids(const skip_problem_t& p);
+// Whether the attention runs without the work list (row tiles).
+bool attn_by_tiles(const skip_problem_t& p);
 // Work list of the bf16 attention launch (depends on the offsets only).
 hipError_t launch_attention_plan(const skip_problem_t& p, const int32_t* kept_offsets,
                                  const int32_t* query_passages,
