@@ -16,8 +16,12 @@
 // stores); the last of them to finish (a counter) sums the partials in slice
 // order and assigns every row by argmin_r |c_r|^2 - 2 v_i . c_r, which is
 // |v_i - c_r|^2 less the row's own |v_i|^2.
+#include <algorithm>
+#include <type_traits>
+
 #include "skip_common.h"
 #include "skip_internal.h"
+#include "skip_select.h"
 
 namespace skip {
 
@@ -599,19 +603,401 @@ region_step_kernel(const T* __restrict__ rows, RegionArgs a) {
   if (tid == 0) a.done[b] = 0;
 }
 
+// ---------------------------------------------------------------------------
+// Small questions: iterations on the Gram matrix of the kept rows.  Every
+// centroid is a start row or the mean of the rows of some assignment, so
+//   v_i . c_r = (1 / n_r) sum_{j in r} v_j . v_i,
+//   |c_r|^2   = (1 / n_r) sum_{i in r} v_i . c_r:
+// the iterations need only G_ij = v_i . v_j (float64 sums), not the rows.
+// Three launches instead of n_iter + 2:
+//   region_gram_kernel     G on the float64 matrix cores, a 16 x 16 tile of
+//                          its lower triangle (and the mirror image) per
+//                          workgroup, a quarter of the columns per wave
+//   region_iterate_kernel  one workgroup per question runs all iterations:
+//                          argmin_r |c_r|^2 - 2 v_i . c_r (ties to the lower
+//                          region), then the sums of G's rows of each region
+//   region_mean_kernel     the centroids: means over each region's last rows
+//                          (its start row if it never had any)
+// Measured against a step launch per iteration (16 questions of 192 rows, d =
+// 4096, R = 8, 10 iterations): 63 + 74 + 14 us, the call 147 us against 310;
+// 96 rows of d = 1024: 71 against 235.  The products grow with the square of
+// the rows: at 384 rows 432 us against 578 (bf16) and 529 against 677
+// (float32), at 512 743 against 777 and 905 against 830, hence the limit; and
+// they do not shrink with the iterations, hence kGramRowsPerIter (10
+// iterations reach the limit).
+constexpr int kGramTile = 16;
+constexpr int kGramMaxRows = 384;        // rows per question
+constexpr int kGramRowsPerIter = 38;     // rows per question and iteration
+constexpr int kGramThreads = 1024;
+constexpr int kGramWaves = kGramThreads / 64;
+constexpr int kGramWords = kGramMaxRows / 64;
+// doubles of the iterations' sums in LDS: R + (R + 15) of the rows
+constexpr int kGramLds = (2 * kRegMax + kGramWaves - 1) * kGramMaxRows;
+
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+
+struct RegionGramArgs {
+  const int32_t* kept_offsets;
+  const int32_t* kept_idx;     // NULL: rows are the kept rows themselves
+  int N, total_kept, B, d, k_max, r_max, n_iter;
+  int ld;                      // rows (and columns) of a question's G
+  double* G;                   // [B][ld][ld]
+  uint64_t* bits;              // [B][kRegMax][kGramWords] rows of each region's centroid
+  int32_t* region_out;
+  float* cent_out;
+  int32_t* sizes_out;          // or NULL
+};
+
+// Tile (I, J <= I) of question b's G.  Lane l supplies row l % 16 of either
+// operand and column slot l / 16: in a group of 4E columns (E = 16 bytes of
+// elements) slot kk of product m is column E kk + m, so a lane reads 16
+// consecutive bytes of its row per group.  Bound by the float64 matrix cores.
+template <typename T, bool IDX>
+__global__ void __launch_bounds__(256)
+region_gram_kernel(const T* __restrict__ rows, RegionGramArgs a, int pairs) {
+  constexpr int E = 16 / (int)sizeof(T);
+  constexpr int U = 4;                               // groups in flight
+  __shared__ double red[4][4][64];
+  // a question's tiles on one XCD: its L2 holds the question's rows
+  const int L = blockIdx.x, b = (L & 7) + 8 * ((L >> 3) / pairs), t = (L >> 3) % pairs;
+  if (b >= a.B) return;
+  int k0, k1;
+  range_of(a.kept_offsets, b, a.total_kept, k0, k1);
+  const int k = min(k1 - k0, a.k_max);
+  int I = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
+  while (I * (I + 1) / 2 > t) --I;
+  while ((I + 1) * (I + 2) / 2 <= t) ++I;
+  const int J = t - I * (I + 1) / 2;
+  if (I * kGramTile >= k) return;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, kk = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  auto row_of = [&](int i) -> const T* {             // rows past the question repeat its last one
+    const int ii = min(i, k - 1);
+    const size_t id = IDX ? (size_t)b * a.N + clampi(a.kept_idx[k0 + ii], 0, a.N - 1)
+                          : (size_t)(k0 + ii);
+    return rows + id * a.d + kk * E;
+  };
+  const T* ra = row_of(I * kGramTile + l16);
+  const T* rb = row_of(J * kGramTile + l16);
+  const int ng = (a.d + 4 * E - 1) / (4 * E);
+  const int g0 = w * ng / 4, g1 = (w + 1) * ng / 4;
+  f64x4_t acc[4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) acc[m] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+  auto load = [&](u32x4 (&xa)[U], u32x4 (&xb)[U], int g) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int c = min(g + u, ng - 1) * 4 * E;      // groups past the wave's are not multiplied
+      // (d is a multiple of 8: whole chunks; a chunk past it reads the first
+      // one and is multiplied as zeros)
+      const int o = c + kk * E < a.d ? c : -kk * E;
+      xa[u] = *reinterpret_cast<const u32x4*>(ra + o);
+      xb[u] = *reinterpret_cast<const u32x4*>(rb + o);
+    }
+  };
+  auto multiply = [&](const u32x4 (&xa)[U], const u32x4 (&xb)[U], int g) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (g + u < g1) {
+        const bool in = (g + u) * 4 * E + kk * E < a.d;
+        double va[E], vb[E];
+        unpack16_f64<T>(in ? xa[u] : u32x4{0u, 0u, 0u, 0u}, va);
+        unpack16_f64<T>(xb[u], vb);
+#pragma unroll
+        for (int m = 0; m < E; ++m)
+          acc[m & 3] = __builtin_amdgcn_mfma_f64_16x16x4f64(va[m], vb[m], acc[m & 3], 0, 0, 0);
+      }
+    }
+  };
+  u32x4 xa0[U], xb0[U], xa1[U], xb1[U];
+  load(xa0, xb0, g0);
+  for (int g = g0; g < g1; g += 2 * U) {
+    load(xa1, xb1, g + U);
+    multiply(xa0, xb0, g);
+    load(xa0, xb0, g + 2 * U);
+    multiply(xa1, xb1, g + U);
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) red[w][v][lane] = ((acc[0][v] + acc[1][v]) + acc[2][v]) + acc[3][v];
+  __syncthreads();
+  // register v of lane l: row 4v + l / 16, column l % 16 of the tile
+  const int v = w, i = I * kGramTile + 4 * v + kk, j = J * kGramTile + l16;
+  // (whole tiles: the padding holds finite values, which meet zeros)
+  const double x = ((red[0][v][lane] + red[1][v][lane]) + red[2][v][lane]) + red[3][v][lane];
+  double* G = a.G + (size_t)b * a.ld * a.ld;
+  G[(size_t)i * a.ld + j] = x;
+  if (I != J) G[(size_t)j * a.ld + i] = x;           // a diagonal tile is whole as it is
+}
+
+// All iterations of one question.  Per iteration the rows of G are read once,
+// sorted by region, and added: bound by the instructions a row takes (one
+// float64 product of G with the one-hot assignment on the matrix cores was
+// twice as slow) and by the latency of the short phases between barriers.
+// RM: a compile-time bound on the regions (the loops over them unroll).
+template <int RM>
+__global__ void __launch_bounds__(kGramThreads)
+region_iterate_kernel(RegionGramArgs a) {
+  // [R][ks] v_i . c_r, then [R + 15][ks] the waves' partial sums of them
+  __shared__ double D[kGramLds];
+  __shared__ double cn[RM];                          // |c_r|^2
+  __shared__ int cnt[RM], start[RM];
+  __shared__ int cw[kGramWords][RM];                 // rows per wave and region
+  __shared__ uint64_t bits[kRegMax][kGramWords];
+  __shared__ int perm[kGramMaxRows];                 // region << 16 | row, sorted
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int k0, k1;
+  range_of(a.kept_offsets, b, a.total_kept, k0, k1);
+  const int k = min(k1 - k0, a.k_max);
+  const int R = regions_of(k, a.r_max);
+  const double* __restrict__ G = a.G + (size_t)b * a.ld * a.ld;
+  const int nb = (k + 63) / 64, ks = nb * 64;
+  double* part = D + R * ks;
+  // wave w sums the sorted positions [q0, q1)
+  const int q0 = w * k / kGramWaves, q1 = (w + 1) * k / kGramWaves, nq = q1 - q0;
+  if (tid < kRegMax * kGramWords) (&bits[0][0])[tid] = 0ull;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < RM; ++r) {                     // start rows
+    if (r >= R) continue;
+    const int pos = ((2 * r + 1) * k) / (2 * R);
+    if (tid < k) D[r * ks + tid] = G[(size_t)pos * a.ld + tid];
+    if (tid == 0) {
+      cn[r] = G[(size_t)pos * a.ld + pos];
+      bits[r][pos >> 6] = 1ull << (pos & 63);
+    }
+  }
+  int best = -1, n = 0;                              // n: rows of region `lane`
+  for (int t = 0; t < a.n_iter && R > 0; ++t) {
+    __syncthreads();
+    uint64_t mine = 0, of_lane = 0;                  // rows of the row's region, of region `lane`
+    if (w < nb) {
+      // nearest centroid of row tid
+      best = -1;
+      if (tid < k) {
+        double dist[RM];
+#pragma unroll
+        for (int r = 0; r < RM; ++r) {
+          const int rr = min(r, R - 1);
+          dist[r] = cn[rr] - 2.0 * D[rr * ks + tid];
+        }
+        best = 0;
+        double bd = dist[0];
+#pragma unroll
+        for (int r = 1; r < RM; ++r)
+          if (r < R && dist[r] < bd) {
+            bd = dist[r];
+            best = r;
+          }
+      }
+#pragma unroll
+      for (int r = 0; r < RM; ++r) {
+        const uint64_t m = __ballot(best == r);
+        if (best == r) mine = m;
+        if (lane == r) of_lane = m;
+      }
+      if (lane < R) cw[w][lane] = (int)__popcll(of_lane);
+    }
+    __syncthreads();
+    // rows sorted by region, each after the earlier waves' and lanes' rows of
+    // its region; a region left without rows keeps its centroid: its rows
+    // stay those of the last assignment that gave it some
+    if (w < nb) {
+      int before = 0;
+      n = 0;
+      if (lane < R)
+        for (int v = 0; v < nb; ++v) {
+          const int x = cw[v][lane];
+          n += x;
+          before += v < w ? x : 0;
+        }
+      const int s0 = (int)wave_incl_scan((uint32_t)n) - n;
+      if (w == 0 && lane < R) {
+        cnt[lane] = n;
+        start[lane] = s0;
+      }
+      if (lane < R && n > 0) bits[lane][w] = of_lane;
+      const int off = __shfl(s0 + before, max(best, 0), kWave) +
+                      (int)__popcll(mine & ((1ull << lane) - 1ull));
+      if (best >= 0) perm[off] = best << 16 | tid;
+    }
+    if (t + 1 == a.n_iter) break;
+    __syncthreads();
+    // v_i . c_r = the sum of G's rows of region r / n_r.  The wave leaves one
+    // partial sum per region it meets, in slot w + r (both grow along the
+    // sorted list, so no two share one); a region's partials are then added in
+    // wave order.
+    if (nq > 0) {
+      const int pr = perm[q0 + min(lane, nq - 1)];   // lane u: position q0 + u
+      const int prev = __shfl_up(pr, 1, kWave);      // (lane 0: its own)
+      const uint64_t turns = uniform64(__ballot((pr >> 16) != (prev >> 16)));
+      auto sums = [&](auto tag, int c0) {            // column blocks c0 .. c0 + NC - 1
+        constexpr int NC = decltype(tag)::value;
+        double* out = part + c0 * 64 + lane;
+        uint32_t off[NC];                            // columns past the question: the last one
+#pragma unroll
+        for (int c = 0; c < NC; ++c) off[c] = (uint32_t)min((c0 + c) * 64 + lane, k - 1);
+        double s[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) s[c] = 0.0;
+        int cur = __builtin_amdgcn_readfirstlane(pr >> 16);
+        for (int u0 = 0; u0 < nq; u0 += 12) {
+          double x[12][NC];
+#pragma unroll
+          for (int u = 0; u < 12; ++u) {
+            const int j = __builtin_amdgcn_readlane(pr, min(u0 + u, nq - 1)) & 0xffff;
+            const double* row = G + (size_t)j * a.ld;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) x[u][c] = row[off[c]];
+          }
+#pragma unroll
+          for (int u = 0; u < 12; ++u) {
+            // (no early exit: the compiler would index the registers)
+            if (u0 + u < nq) {
+              if ((turns >> (u0 + u)) & 1ull) {
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                  out[(w + cur) * ks + 64 * c] = s[c];
+                  s[c] = 0.0;
+                }
+                cur = __builtin_amdgcn_readlane(pr, u0 + u) >> 16;
+              }
+#pragma unroll
+              for (int c = 0; c < NC; ++c) s[c] += x[u][c];
+            }
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) out[(w + cur) * ks + 64 * c] = s[c];
+      };
+      int c0 = 0;
+      for (; c0 + 3 <= nb; c0 += 3) sums(std::integral_constant<int, 3>{}, c0);
+      if (nb - c0 == 2) sums(std::integral_constant<int, 2>{}, c0);
+      if (nb - c0 == 1) sums(std::integral_constant<int, 1>{}, c0);
+    }
+    __syncthreads();
+    for (int u = w; u < R * nb; u += kGramWaves) {
+      const int r = u / nb, i = (u - r * nb) * 64 + lane;
+      const int m = __builtin_amdgcn_readfirstlane(cnt[r]);
+      const int st = __builtin_amdgcn_readfirstlane(start[r]);
+      if (m == 0) continue;
+      // the waves that hold positions st .. st + m - 1 (position p: wave
+      // ((p + 1) 16 - 1) / k; at fewer rows than waves some hold none)
+      const int w0 = ((st + 1) * kGramWaves - 1) / k, w1 = ((st + m) * kGramWaves - 1) / k;
+      double s = 0.0;
+      for (int v = w0; v <= w1; ++v)
+        if ((v + 1) * k / kGramWaves > v * k / kGramWaves) s += part[(v + r) * ks + i];
+      D[r * ks + i] = s / (double)m;
+    }
+    __syncthreads();
+    // |c_r|^2: one wave a region
+    if (w < R && cnt[w] > 0) {
+      double s = 0.0;
+      for (int q = lane; q < cnt[w]; q += 64) s += D[w * ks + (perm[start[w] + q] & 0xffff)];
+      s = wave_sum_f64(s);
+      if (lane == 0) cn[w] = s / (double)cnt[w];
+    }
+  }
+  if (tid < k) a.region_out[k0 + tid] = best;
+  if (a.sizes_out && tid < a.r_max) a.sizes_out[b * a.r_max + tid] = n;
+  __syncthreads();
+  if (tid < kRegMax * kGramWords)
+    a.bits[(size_t)b * kRegMax * kGramWords + tid] = (&bits[0][0])[tid];
+}
+
+// Centroids: workgroup = one wave = (256 columns, question, region), lane =
+// four columns; the rows of the region's bit set are listed in LDS and summed
+// in ascending order, sixteen loads in flight.
+template <typename T, bool IDX>
+__global__ void __launch_bounds__(64)
+region_mean_kernel(const T* __restrict__ rows, RegionGramArgs a) {
+  __shared__ int ids[kGramMaxRows];
+  const int b = blockIdx.y, r = blockIdx.z, lane = threadIdx.x;
+  int k0, k1;
+  range_of(a.kept_offsets, b, a.total_kept, k0, k1);
+  const int k = min(k1 - k0, a.k_max);
+  const int c = blockIdx.x * 256 + 4 * lane;
+  const int cc = c < a.d ? c : 0;                    // d is a multiple of 8
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  int n = 0;
+  if (r < regions_of(k, a.r_max)) {
+    for (int v = 0; v * 64 < k; ++v) {
+      const uint64_t m = uniform64(a.bits[((size_t)b * kRegMax + r) * kGramWords + v]);
+      if ((m >> lane) & 1ull) {
+        const int i = v * 64 + lane;
+        ids[n + (int)__popcll(m & ((1ull << lane) - 1ull))] =
+            IDX ? b * a.N + clampi(a.kept_idx[k0 + i], 0, a.N - 1) : k0 + i;
+      }
+      n += (int)__popcll(m);
+    }
+    __syncthreads();
+    for (int q0 = 0; q0 < n; q0 += 16) {
+      T x[16][4];
+#pragma unroll
+      for (int q = 0; q < 16; ++q)
+        __builtin_memcpy(x[q], __builtin_assume_aligned(
+                                   rows + (size_t)ids[min(q0 + q, n - 1)] * a.d + cc,
+                                   4 * sizeof(T)), 4 * sizeof(T));
+#pragma unroll
+      for (int q = 0; q < 16; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (q0 + q < n) s[e] += reg_load1<T>(&x[q][e]);
+    }
+  }
+  if (c < a.d)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      a.cent_out[((size_t)b * a.r_max + r) * a.d + c + e] = n > 0 ? (float)(s[e] / (double)n) : 0.f;
+}
+
 static size_t ralign(size_t n) { return (n + 255) & ~(size_t)255; }
+
+static int gram_ld(const skip_problem_t& p) { return (p.k_max + 15) / 16 * 16; }
+
+// Whether the iterations may run on the Gram matrix, and whether they do.
+static bool gram_shape(const skip_problem_t& p) { return p.k_max <= kGramMaxRows; }
+static bool regions_by_gram(const skip_problem_t& p, int n_iter) {
+  return gram_shape(p) && p.k_max <= (long long)kGramRowsPerIter * n_iter;
+}
+
+static size_t gram_scratch_bytes(const skip_problem_t& p) {
+  return ralign((size_t)p.B * gram_ld(p) * gram_ld(p) * sizeof(double)) +
+         ralign((size_t)p.B * kRegMax * kGramWords * sizeof(uint64_t));
+}
+
+template <typename T, bool IDX>
+static hipError_t launch_gram(const skip_problem_t& p, const T* rows, const RegionGramArgs& a,
+                              hipStream_t s) {
+  if (p.k_max > 0) {
+    const int nt = (p.k_max + kGramTile - 1) / kGramTile, pairs = nt * (nt + 1) / 2;
+    const long long grid = 8ll * ((p.B + 7) / 8) * pairs;
+    if (grid > INT32_MAX) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((region_gram_kernel<T, IDX>), dim3((unsigned)grid), dim3(256), 0, s, rows,
+                       a, pairs);
+  }
+  const dim3 grid(p.B), block(kGramThreads);
+  if (a.r_max <= 4) hipLaunchKernelGGL(region_iterate_kernel<4>, grid, block, 0, s, a);
+  else if (a.r_max <= 8) hipLaunchKernelGGL(region_iterate_kernel<8>, grid, block, 0, s, a);
+  else hipLaunchKernelGGL(region_iterate_kernel<16>, grid, block, 0, s, a);
+  hipLaunchKernelGGL((region_mean_kernel<T, IDX>), dim3((p.d + 255) / 256, p.B, a.r_max),
+                     dim3(64), 0, s, rows, a);
+  return hipGetLastError();
+}
 
 int region_slices(const skip_problem_t& p) { return (p.d + kRegCols - 1) / kRegCols; }
 
 size_t region_scratch_bytes(const skip_problem_t& p, int r_max) {
   const size_t S = (size_t)region_slices(p);
-  return ralign((size_t)p.B * r_max * p.d * sizeof(double)) +
+  const size_t gram = gram_shape(p) ? gram_scratch_bytes(p) : 0;
+  const size_t steps = ralign((size_t)p.B * r_max * p.d * sizeof(double)) +
          ralign((size_t)p.B * S * (p.k_max + 1) * r_max * sizeof(double)) +
          ralign((size_t)p.total_kept) +
          ralign((size_t)p.total_kept * sizeof(int32_t)) +
          ralign((size_t)p.total_kept) +
          ralign((size_t)p.B * r_max * sizeof(int32_t)) +
          ralign((size_t)p.B * sizeof(int32_t));
+  return std::max(gram, steps);
 }
 
 template <typename T, bool IDX>
@@ -630,6 +1016,30 @@ hipError_t launch_regions(const skip_problem_t& p, const void* rows, const int32
                           float* centroids, int32_t* sizes, void* scratch, hipStream_t s) {
   const int S = region_slices(p);
   char* c = static_cast<char*>(scratch);
+  if (regions_by_gram(p, n_iter)) {
+    RegionGramArgs g;
+    g.kept_offsets = kept_offsets;
+    g.kept_idx = kept_idx;
+    g.N = p.N;
+    g.total_kept = p.total_kept;
+    g.B = p.B;
+    g.d = p.d;
+    g.k_max = p.k_max;
+    g.r_max = r_max;
+    g.n_iter = n_iter;
+    g.ld = gram_ld(p);
+    g.G = reinterpret_cast<double*>(c);
+    g.bits = reinterpret_cast<uint64_t*>(
+        c + ralign((size_t)p.B * g.ld * g.ld * sizeof(double)));
+    g.region_out = region;
+    g.cent_out = centroids;
+    g.sizes_out = sizes;
+    if (p.dtype == SKIP_F32)
+      return kept_idx ? launch_gram<float, true>(p, (const float*)rows, g, s)
+                      : launch_gram<float, false>(p, (const float*)rows, g, s);
+    return kept_idx ? launch_gram<bf16_t, true>(p, (const bf16_t*)rows, g, s)
+                    : launch_gram<bf16_t, false>(p, (const bf16_t*)rows, g, s);
+  }
   RegionArgs a;
   a.kept_offsets = kept_offsets;
   a.kept_idx = kept_idx;

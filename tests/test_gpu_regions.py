@@ -125,3 +125,34 @@ def test_regions_full_size(B):
     torch.cuda.synchronize()
     check_regions(batch, kept, region, cent, sizes, 8, 10, "highres")
     assert int(sizes.sum()) == int(batch.k.sum())
+
+
+@pytest.mark.parametrize("wl,H,d_h,k,r_max,n_iter", [
+    ("llava_bf16", 1, 8, (1, 4, 15, 16, 17), 4, 1),       # less than a group of columns
+    ("tiny_fp32", 3, 40, (31, 32, 33, 38), 16, 1),        # the last rows of one iteration's rule
+    ("tiny_fp32", 3, 40, (39,), 16, 1),                   # past it: a launch per step
+    ("llava_bf16", 5, 64, (63, 64, 65, 97), 8, 7),
+    ("llava_bf16", 3, 64, (383, 384), 16, 11),            # the largest Gram matrix
+    ("llava_bf16", 3, 64, (384, 385), 16, 11),            # past it
+])
+def test_regions_gram_edges(B, wl, H, d_h, k, r_max, n_iter):
+    """Both sides of the rule that takes small questions to the Gram matrix,
+    and its tiles' edges.  Two of the start rows are equal, so the higher of
+    their regions is left without rows and keeps its centroid."""
+    batch = wls.make_batch(wl, 23, B=5, N=400, H=H, d_h=d_h, T=(2,), k=k)
+    V = batch.V.clone()
+    kept = [np.arange(int(n), dtype=np.int64) + 3 for n in batch.k]
+    for b, n in enumerate(int(x) for x in batch.k):
+        R = orc.region_count(n, r_max)
+        if R >= 3:
+            pos = [((2 * r + 1) * n) // (2 * R) + 3 for r in (1, 2)]
+            V[b, pos[1]] = V[b, pos[0]]
+    batch.V = V
+    db = B.to_device(batch)
+    idx = torch.from_numpy(np.concatenate(kept).astype(np.int32)).cuda()
+    out = B.region_kmeans(db, db.V, kept_idx=idx, r_max=r_max, n_iter=n_iter)
+    torch.cuda.synchronize()
+    check_regions(batch, kept, *out, r_max, n_iter, f"{wl} k={k}")
+    if n_iter == 1:
+        n, R = int(batch.k[0]), orc.region_count(int(batch.k[0]), r_max)
+        assert R < 3 or int(out[2][0, 2]) == 0
