@@ -301,6 +301,7 @@ mlp_score_kernel(const bf16_t* __restrict__ V, int N, int d, int B,
     // load, while there is one) and the W1 fragments of step s+1 (four loads)
     if (s + 2 < ksteps) wait_vmcnt<5>();
     else wait_vmcnt<4>();
+    wait_lgkm0();                                    // the wave's Hadamard chunks are written
     barrier_nofence();
     if (s + kMlpAhead < ksteps) issue_v(s + kMlpAhead);
     mma_step(s, w);

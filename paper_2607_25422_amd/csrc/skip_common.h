@@ -56,6 +56,13 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
   asm volatile("" ::: "memory");
 }
+// Wait until this wave's LDS operations have completed (vmcnt and expcnt left
+// unconstrained).
+__device__ __forceinline__ void wait_lgkm0() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);
+  asm volatile("" ::: "memory");
+}
 // Workgroup barrier without a memory fence: the waves that write LDS wait for
 // their own writes (vmcnt for direct loads, lgkmcnt for LDS stores) before it.
 __device__ __forceinline__ void barrier_nofence() {
