@@ -278,72 +278,92 @@ __device__ __forceinline__ long long edges_of_question(int k, int P, int rule,
   return (long long)fmin((double)n, fmax(0.0, want));
 }
 
-// Candidate keys, one thread per (row, passage) of a question: the slice
-// partials of the dot product (and of both squared norms) summed in slice
-// order, the cosine (or the scaled dot product) formed from them, and its
-// order-preserving key written over slice 0 of the partials; a passage the
-// verification gate dropped gets the lowest key.  Each candidate's partials
-// are read and its key written by one thread only.
+// Key of candidate (row i, passage j) of question b: the slice partials of the
+// dot product (and of both squared norms) summed in slice order, U loads in
+// flight, the cosine (or the scaled dot product) formed from them, and its
+// order-preserving key; a passage the verification gate dropped gets the
+// lowest key.
+struct CandidateArgs {
+  const double *part, *qn2p, *kn2p;
+  int S, k_max, P_max, d, metric;
+};
+template <int U>
+__device__ __forceinline__ uint64_t candidate_key(const CandidateArgs& a, int b, int i, int j,
+                                                  bool kept) {
+  // sum of S values at base + s * stride (slices clamped into range, so that
+  // every load of a batch is unconditional)
+  auto slice_sum = [&](const double* base, size_t stride) -> double {
+    double acc = 0.0;
+    for (int sl0 = 0; sl0 < a.S; sl0 += U) {
+      double x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) x[u] = base[(size_t)min(sl0 + u, a.S - 1) * stride];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (sl0 + u < a.S) acc += x[u];
+    }
+    return acc;
+  };
+  const double dot = slice_sum(a.part + ((size_t)b * a.S * a.k_max + i) * a.P_max + j,
+                               (size_t)a.k_max * a.P_max);
+  double c;
+  if (a.metric == SKIP_EDGE_DOT) {
+    c = dot * (1.0 / sqrt((double)a.d));
+  } else {
+    const double nq = sqrt(slice_sum(a.qn2p + (size_t)b * a.S * a.k_max + i, (size_t)a.k_max));
+    const double nk = sqrt(slice_sum(a.kn2p + (size_t)b * a.S * a.P_max + j, (size_t)a.P_max));
+    c = (nq > 0.0 && nk > 0.0) ? dot / (nq * nk) : 0.0;
+  }
+  return kept ? order_key(c) : 0ull;
+}
+
+// Candidate keys, one thread per (row, passage) of a question, written over
+// slice 0 of the partials: each candidate's partials are read and its key
+// written by one thread only.
 __global__ void __launch_bounds__(256)
-edge_keys_kernel(double* __restrict__ part, const double* __restrict__ qn2p,
-                 const double* __restrict__ kn2p, int S,
+edge_keys_kernel(double* __restrict__ part, CandidateArgs a,
                  const int32_t* __restrict__ kept_offsets,
                  const int32_t* __restrict__ query_passages, int total_kept,
-                 int total_passages, int k_max, int P_max, int d, int metric,
-                 const uint8_t* __restrict__ keep) {
+                 int total_passages, const uint8_t* __restrict__ keep) {
   const int b = blockIdx.y;
   int k0, k1, p0, p1;
   range_of(kept_offsets, b, total_kept, k0, k1);
   range_of(query_passages, b, total_passages, p0, p1);
-  const int k = min(k1 - k0, k_max);
-  const int P = min(min(p1 - p0, P_max), 64);
+  const int k = min(k1 - k0, a.k_max);
+  const int P = min(min(p1 - p0, a.P_max), 64);
   const int n = min(k * P, kGSelThreads * kGSelMaxPT);
   const int f = blockIdx.x * blockDim.x + threadIdx.x;
   if (f >= n) return;
   const int i = f / P, j = f - i * P;
-  // sum of S values at base + s * stride, in slice order (slices clamped
-  // into range, so that every load of a batch is unconditional)
-  auto slice_sum = [&](const double* base, size_t stride) -> double {
-    double acc = 0.0;
-    for (int sl0 = 0; sl0 < S; sl0 += 16) {
-      double x[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) x[u] = base[(size_t)min(sl0 + u, S - 1) * stride];
-#pragma unroll
-      for (int u = 0; u < 16; ++u)
-        if (sl0 + u < S) acc += x[u];
-    }
-    return acc;
-  };
-  double* cand = part + ((size_t)b * S * k_max + i) * P_max + j;
-  const double dot = slice_sum(cand, (size_t)k_max * P_max);
-  double c;
-  if (metric == SKIP_EDGE_DOT) {
-    c = dot * (1.0 / sqrt((double)d));
-  } else {
-    const double nq = sqrt(slice_sum(qn2p + (size_t)b * S * k_max + i, (size_t)k_max));
-    const double nk = sqrt(slice_sum(kn2p + (size_t)b * S * P_max + j, (size_t)P_max));
-    c = (nq > 0.0 && nk > 0.0) ? dot / (nq * nk) : 0.0;
-  }
-  const bool kept = keep ? keep[p0 + j] != 0 : true;
-  *reinterpret_cast<uint64_t*>(cand) = kept ? order_key(c) : 0ull;
+  a.part = part;
+  const uint64_t key = candidate_key<16>(a, b, i, j, keep ? keep[p0 + j] != 0 : true);
+  reinterpret_cast<uint64_t*>(part)[((size_t)b * a.S * a.k_max + i) * a.P_max + j] = key;
 }
 
+// FORM: the workgroup forms the candidates' keys itself, one a thread (no key
+// launch).  One CU then reads 24 S bytes a candidate, so only small questions
+// take this form (form_in_select).  Bound by the latency of its phases: 97
+// rows x 5 passages, 4 slices: 7.3 us after a key launch of 4.0 before, 5.2 us
+// now.
+template <int MAXPT, bool FORM>
 __global__ void __launch_bounds__(kGSelThreads)
-edge_select_kernel(const double* __restrict__ part, int S,
+edge_select_kernel(CandidateArgs ca,
                    const int32_t* __restrict__ kept_offsets,
                    const int32_t* __restrict__ query_passages, int B, int total_kept,
-                   int total_passages, int k_max, int P_max, double avg_degree,
+                   int total_passages, double avg_degree,
                    int rule, double beta, const uint8_t* __restrict__ keep,
                    uint64_t* __restrict__ rowmask, int32_t* __restrict__ rowptr_out,
                    int32_t* __restrict__ col_out, PlanArgs plan) {
+  const int S = ca.S, k_max = ca.k_max, P_max = ca.P_max;
   __shared__ SelectShared sh;
   __shared__ uint32_t scan_sh[20];
-  __shared__ uint8_t flag[kGSelThreads * kGSelMaxPT];
+  __shared__ uint8_t flag[kGSelThreads * MAXPT];
   // the keys of the per-row cut (the work list builder's LDS in the extra
   // workgroup)
-  __shared__ __align__(16) uint64_t rkeys[kGSelThreads * kGSelMaxPT];
-  static_assert(sizeof(PlanLds) <= sizeof(rkeys), "the work list builder reuses the key LDS");
+  constexpr size_t kKeyLds = kGSelThreads * MAXPT * sizeof(uint64_t);
+  __shared__ __align__(16) uint64_t
+      rkeys[(kKeyLds > sizeof(PlanLds) ? kKeyLds : sizeof(PlanLds)) / sizeof(uint64_t)];
+  static_assert(sizeof(PlanLds) % sizeof(uint64_t) == 0, "the work list builder reuses the key LDS");
   if ((int)blockIdx.x == B) {
     // the extra workgroup: the attention's work list (it depends on the
     // offsets only)
@@ -359,7 +379,7 @@ edge_select_kernel(const double* __restrict__ part, int S,
   range_of(query_passages, b, total_passages, p0, p1);
   const int k = min(k1 - k0, k_max);
   const int P = min(min(p1 - p0, P_max), 64);
-  const int n = min(k * P, kGSelThreads * kGSelMaxPT);
+  const int n = min(k * P, kGSelThreads * MAXPT);
   // passages the verification gate dropped take no edge and do not count in
   // the budget: their candidates get the lowest key
   uint64_t pkeep = (P >= 64) ? ~0ull : ((1ull << P) - 1ull);
@@ -373,23 +393,25 @@ edge_select_kernel(const double* __restrict__ part, int S,
   const int C = (n + blockDim.x - 1) / blockDim.x;
   const int e0 = threadIdx.x * C;
   const int cnt = max(0, min(C, n - e0));
-  // the candidates' keys, formed by the key launch over slice 0 of the
-  // partials
-  const uint64_t* ck = reinterpret_cast<const uint64_t*>(part) + (size_t)b * S * k_max * P_max;
-  uint64_t keys[kGSelMaxPT];
+  // the candidates' keys: formed here, or by the key launch over slice 0 of
+  // the partials
+  const uint64_t* ck =
+      reinterpret_cast<const uint64_t*>(ca.part) + (size_t)b * S * k_max * P_max;
+  uint64_t keys[MAXPT];
 #pragma unroll
-  for (int jj = 0; jj < kGSelMaxPT; ++jj) {
+  for (int jj = 0; jj < MAXPT; ++jj) {
     keys[jj] = 0ull;
     if (jj < cnt) {
       const int f = e0 + jj, ii = f / P;
-      keys[jj] = ck[(size_t)ii * P_max + (f - ii * P)];
+      keys[jj] = FORM ? candidate_key<4>(ca, b, ii, f - ii * P, (pkeep >> (f - ii * P)) & 1ull)
+                      : ck[(size_t)ii * P_max + (f - ii * P)];
     }
   }
   uint32_t flags;
   if (rule == SKIP_EDGE_ROW_TOP) {
     // every row keeps its D largest (lower passage first on ties)
 #pragma unroll
-    for (int jj = 0; jj < kGSelMaxPT; ++jj)
+    for (int jj = 0; jj < MAXPT; ++jj)
       if (jj < cnt) rkeys[e0 + jj] = keys[jj];
     __syncthreads();
     const int D = (int)fmin((double)Pk, ceil(avg_degree));
@@ -408,12 +430,12 @@ edge_select_kernel(const double* __restrict__ part, int S,
     __syncthreads();
     flags = 0u;
 #pragma unroll
-    for (int jj = 0; jj < kGSelMaxPT; ++jj)
+    for (int jj = 0; jj < MAXPT; ++jj)
       if (jj < cnt && flag[e0 + jj]) flags |= 1u << jj;
   } else {
-    flags = block_select_top_wide<kGSelMaxPT>(keys, cnt, n, E, &sh);
+    flags = block_select_top_wide<MAXPT>(keys, cnt, n, E, &sh);
 #pragma unroll
-    for (int j = 0; j < kGSelMaxPT; ++j)
+    for (int j = 0; j < MAXPT; ++j)
       if (j < cnt) flag[e0 + j] = (flags >> j) & 1u;
     __syncthreads();
   }
@@ -426,8 +448,10 @@ edge_select_kernel(const double* __restrict__ part, int S,
   if (rowptr_out == nullptr || col_out == nullptr) return;
 
   // CSR: the edges of question b start after those of questions 0..b-1.
+  // (one earlier question a lane, summed over the wave: their offsets arrive
+  // together instead of one question's after another's)
   long long base = 0;
-  for (int bb = 0; bb < b; ++bb) {
+  for (int bb = threadIdx.x & (kWave - 1); bb < b; bb += kWave) {
     int a0, a1, q0, q1;
     range_of(kept_offsets, bb, total_kept, a0, a1);
     range_of(query_passages, bb, total_passages, q0, q1);
@@ -439,11 +463,13 @@ edge_select_kernel(const double* __restrict__ part, int S,
     }
     base += edges_of_question(kq, Pkq, rule, avg_degree, beta);
   }
+#pragma unroll
+  for (int sh = 32; sh >= 1; sh >>= 1) base += __shfl_xor(base, sh, kWave);
   uint32_t total;
   uint32_t pos = block_exclusive_scan(__popc(flags), scan_sh, &total);
   const long long cap = (long long)total_kept * P_max;
 #pragma unroll
-  for (int j = 0; j < kGSelMaxPT; ++j) {
+  for (int j = 0; j < MAXPT; ++j) {
     if (j < cnt) {
       const int f = e0 + j;
       if (P > 0 && f % P == 0) {
@@ -531,6 +557,14 @@ hipError_t launch_edge_dot(const skip_problem_t& p, QuerySource q,
   return hipGetLastError();
 }
 
+// Whether the selection forms the candidates' keys itself: one candidate a
+// thread, and few enough slices that one CU reads them (at most 196 KB, about
+// 1.5 us) in less time than the key launch takes (4 us; 16 slices of two
+// candidates a thread would be 740 KB, more than the launch).
+static bool form_in_select(const skip_problem_t& p) {
+  return (long long)p.k_max * std::min(p.P_max, 64) <= kGSelThreads && edge_slices(p) <= 8;
+}
+
 hipError_t launch_edge_select(const skip_problem_t& p, EdgePartials ep,
                               const int32_t* kept_offsets, const int32_t* query_passages,
                               uint64_t* rowmask, int32_t* rowptr_out, int32_t* col_out,
@@ -546,22 +580,28 @@ hipError_t launch_edge_select(const skip_problem_t& p, EdgePartials ep,
     pa.total_tokens = p.total_tokens;
     pa.n_ids = (int)n_ids;
   }
-  const int S = edge_slices(p);
-  if (p.total_kept > 0 && p.k_max > 0 && p.P_max > 0) {
+  const CandidateArgs ca{ep.part, ep.qn2,  ep.kn2, edge_slices(p),
+                         p.k_max, p.P_max, p.d,    p.edge_metric};
+  const bool form = form_in_select(p);
+  if (!form && p.total_kept > 0 && p.k_max > 0 && p.P_max > 0) {
     // the candidates' keys from the partials of the dot-product launch
     const int n = (int)std::min<long long>((long long)p.k_max * std::min(p.P_max, 64),
                                            (long long)kGSelThreads * kGSelMaxPT);
     hipLaunchKernelGGL(edge_keys_kernel, dim3((n + 255) / 256, p.B), dim3(256), 0, s, ep.part,
-                       ep.qn2, ep.kn2, S, kept_offsets, query_passages, p.total_kept,
-                       p.total_passages, p.k_max, p.P_max, p.d, p.edge_metric, passage_keep);
+                       ca, kept_offsets, query_passages, p.total_kept, p.total_passages,
+                       passage_keep);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(edge_select_kernel, dim3(p.B + (n_ids > 0 ? 1 : 0)), dim3(kGSelThreads),
-                     0, s, ep.part, S, kept_offsets, query_passages, p.B, p.total_kept,
-                     p.total_passages, p.k_max, p.P_max, p.avg_degree, p.edge_rule,
-                     p.edge_beta, passage_keep, rowmask, rowptr_out, col_out, pa);
-  return hipGetLastError();
+  auto select = [&](auto kernel) -> hipError_t {
+    hipLaunchKernelGGL(kernel, dim3(p.B + (n_ids > 0 ? 1 : 0)), dim3(kGSelThreads), 0, s, ca,
+                       kept_offsets, query_passages, p.B, p.total_kept, p.total_passages,
+                       p.avg_degree, p.edge_rule, p.edge_beta, passage_keep, rowmask, rowptr_out,
+                       col_out, pa);
+    return hipGetLastError();
+  };
+  return form ? select(edge_select_kernel<1, true>)
+              : select(edge_select_kernel<kGSelMaxPT, false>);
 }
 
 hipError_t launch_csr_to_mask(const skip_problem_t& p, const int32_t* kept_offsets,

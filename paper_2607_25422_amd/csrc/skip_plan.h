@@ -32,7 +32,7 @@ struct PlanLds {
 
 // The whole block builds the list; scan_sh holds blockDim.x / 64 + 1 words.
 // Contains __syncthreads().
-__device__ inline void build_attention_plan(PlanLds& L, uint32_t* scan_sh,
+__device__ __forceinline__ void build_attention_plan(PlanLds& L, uint32_t* scan_sh,
                                             const int32_t* __restrict__ kept_offsets,
                                             const int32_t* __restrict__ query_passages,
                                             const int32_t* __restrict__ passage_offsets,
