@@ -138,6 +138,40 @@ def test_project_packed_matches_one_call(B, d_out):
             assert torch.equal(one, two) and torch.equal(one, three), (seed, out_f32)
 
 
+@pytest.mark.parametrize("d", [32, 64, 96, 160, 320])
+@pytest.mark.parametrize("M,d_out", [(1, 256), (95, 256), (97, 512), (97, 8192), (193, 8192),
+                                     (100, 65536), (192, 65536), (484, 65536)])
+def test_project_tile_edges(B, M, d_out, d):
+    """Few rows (waves split the contraction, some without a part of it), tiles
+    of 96 and of 192 rows (the last three), with remainders of rows and of
+    steps: gathered rows, both outputs, packed and one-call, against float64
+    within the bound above."""
+    say(f"projection tiles M={M} d_out={d_out} d={d}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + d)
+    N, k0 = 600, M // 3
+    V = torch.randn(2, N, d, generator=g, device="cuda").bfloat16()
+    W = (torch.randn(d_out, d, generator=g, device="cuda") / d ** 0.5).bfloat16()
+    o = dict(q_offsets=[0, 1, 2], kept_offsets=[0, k0, M], passage_offsets=[0, 1, 2],
+             query_passages=[0, 1, 2])
+    o = {n: np.array(a, dtype=np.int32) for n, a in o.items()}
+    p = B.make_problem("bf16", B=2, N=N, d=d, H=1, d_h=d, avg_degree=4.0, sm_scale=1.0, **o)
+    t = {n: torch.from_numpy(a).cuda() for n, a in o.items()}
+    db = B.DeviceBatch(p=p, V=V, Qtok=V[0, :2], Kh=V[0, :2].view(2, 1, d),
+                       Vh=V[0, :2].view(2, 1, d), w_bias=None,
+                       workspace=torch.empty(256, dtype=torch.uint8, device="cuda"), **t)
+    idx = torch.cat([torch.randperm(N, generator=g, device="cuda")[:n].sort().values
+                     for n in (k0, M - k0)]).int()
+    rows = torch.cat([V[0][idx[:k0].long()], V[1][idx[k0:].long()]])
+    y32 = B.gather_project(db, V, W, kept_idx=idx, out_f32=True)
+    y = B.gather_project_packed(db, rows, B.pack_projection(db, W), d_out)
+    torch.cuda.synchronize()
+    ref = rows.double() @ W.double().t()
+    bound = (d / 16 + 2) * 2.0 ** -24 * (rows.double().abs() @ W.double().abs().t())
+    assert bool(((y32.double() - ref).abs() <= bound).all())
+    assert torch.equal(y32.to(torch.bfloat16), y)
+
+
 def test_project_full_size(B):
     """highres_bf16: 3072 kept rows read in place through the kept indices,
     W 4096 x 4096; 64 sampled rows checked against the oracle, all columns."""
