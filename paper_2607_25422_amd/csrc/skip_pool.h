@@ -145,25 +145,29 @@ __device__ __forceinline__ void pool_block(const PoolRanges<T>& rg, int j, int s
   }
 }
 
-// The pooling launch: CH = 1, Q = 8, twice the workgroups and a question of up
-// to 32 tokens in one round of loads (a latency each): 16 questions of 32
-// tokens, d = 4096, 8.2 -> 5.5 us; 19 tokens of d = 1024, 4.9 -> 3.2 us (its last
-// rows came one after another); 45 passages of 37..301 tokens, d = 2048, and 6
-// questions, 15.6 -> 9.1 us each.
 // One launch serves two independent sets of ranges: the questions (ranges
 // 0..nq-1 of Qtok, written as the scoring vector) and the passages (the
 // following ranges of Kh, written as their mean).  counters (or NULL): the
 // per-question completion counters of the scoring launch, cleared here.
-template <typename T>
+template <typename T, int CH, int Q>
 __global__ void __launch_bounds__(256)
 pool_kernel(PoolRanges<T> qr, const T* __restrict__ w, PoolRanges<T> pr, int d,
             int32_t* __restrict__ counters) {
-  __shared__ double part[4 * 64 * Vec16<T>::n];
+  __shared__ double part[4 * 64 * CH * Vec16<T>::n];
   const bool question = (int)blockIdx.y < qr.n;
   const int j = question ? (int)blockIdx.y : (int)blockIdx.y - qr.n;
   if (counters && question && blockIdx.x == 0 && threadIdx.x == 0) counters[j] = 0;
-  pool_block<T, 1, 8>(question ? qr : pr, j, blockIdx.x, question, w, d, part);
+  pool_block<T, CH, Q>(question ? qr : pr, j, blockIdx.x, question, w, d, part);
 }
+
+// Few ranges (fewer than kPoolFew workgroups of the form beside the scoring):
+// CH = 1, Q = 8, twice the workgroups and a question of up to 32 tokens in one
+// round of loads, a latency each: 16 questions of 32 tokens, d = 4096, 8.2 ->
+// 5.5 us; 19 tokens of d = 1024, 4.9 -> 3.2 us (its last rows came one after
+// another); 45 passages of 37..301 tokens, d = 2048, and 6 questions, 15.6 ->
+// 9.1 us each.  Many ranges are bound by HBM and keep the longer runs of a row:
+// 160 passages of 256 tokens, d = 4096 (640 workgroups), 60 us against 70.
+constexpr long long kPoolFew = 512;
 
 // Questions (Qtok by q_offsets -> u, nq ranges) and passages (Kh by
 // passage_offsets -> kbar, np ranges); either set may be empty.
@@ -173,24 +177,24 @@ inline hipError_t launch_pools(int dtype, int d, const void* Qtok, const int32_t
                                int total_tokens, double* kbar, hipStream_t s,
                                int32_t* counters = nullptr) {
   if (nq + np <= 0) return hipSuccess;
-  if (dtype == SKIP_F32) {
-    dim3 grid((d + 255) / 256, nq + np);
-    hipLaunchKernelGGL(pool_kernel<float>, grid, dim3(256), 0, s,
-                       PoolRanges<float>{(const float*)Qtok, q_offsets, nq, total_qtok, u},
-                       (const float*)w,
-                       PoolRanges<float>{(const float*)Kh, passage_offsets, np, total_tokens,
-                                         kbar},
-                       d, counters);
-  } else {
-    dim3 grid((d + 511) / 512, nq + np);
-    hipLaunchKernelGGL(pool_kernel<bf16_t>, grid, dim3(256), 0, s,
-                       PoolRanges<bf16_t>{(const bf16_t*)Qtok, q_offsets, nq, total_qtok, u},
-                       (const bf16_t*)w,
-                       PoolRanges<bf16_t>{(const bf16_t*)Kh, passage_offsets, np,
-                                          total_tokens, kbar},
-                       d, counters);
-  }
-  return hipGetLastError();
+  auto slices = [&](int chunks) {
+    const int cols = 64 * chunks * (dtype == SKIP_F32 ? Vec16<float>::n : Vec16<bf16_t>::n);
+    return (d + cols - 1) / cols;
+  };
+  auto go = [&](auto tag, auto kernel, int chunks) -> hipError_t {
+    using T = decltype(tag);
+    hipLaunchKernelGGL(kernel, dim3(slices(chunks), nq + np), dim3(256), 0, s,
+                       PoolRanges<T>{(const T*)Qtok, q_offsets, nq, total_qtok, u}, (const T*)w,
+                       PoolRanges<T>{(const T*)Kh, passage_offsets, np, total_tokens, kbar}, d,
+                       counters);
+    return hipGetLastError();
+  };
+  if ((long long)slices(kPoolChunks) * (nq + np) < kPoolFew)
+    return dtype == SKIP_F32 ? go(float{}, pool_kernel<float, 1, 8>, 1)
+                             : go(bf16_t{}, pool_kernel<bf16_t, 1, 8>, 1);
+  return dtype == SKIP_F32
+             ? go(float{}, pool_kernel<float, kPoolChunks, kPoolRows>, kPoolChunks)
+             : go(bf16_t{}, pool_kernel<bf16_t, kPoolChunks, kPoolRows>, kPoolChunks);
 }
 
 }  // namespace skip
