@@ -128,6 +128,12 @@ def measure_ceilings(torch) -> dict:
                     "16384^3 bf16 GEMM (torch.matmul)"}
 
 
+def attention_kernel(p, dtype):
+    """Name of the kernel that runs the attention (the rule of the library)."""
+    tiles = p.B * p.H * ((p.k_max + 15) // 16) * p.d_h <= 768 * 64
+    return "attn_tile_kernel" if dtype != "bf16" or tiles else "attn_sparse_kernel"
+
+
 def measured_traffic(workload: str):
     """HBM bytes per attention launch from the committed counter summary, or
     None when it was taken on another workload or an older attention source."""
@@ -438,7 +444,7 @@ def bench_regions(args):
                    "r_max": args.r_max, "iterations": args.kmeans_iter, "seed": args.seed},
         "step_gpu_ms": {"p10": round(ms[n // 10], 5), "p50": round(ms[n // 2], 5),
                         "p90": round(ms[min(n - 1, 9 * n // 10)], 5)},
-        "roofline": {"kernel": "region_step_kernel (over the whole call)", "bound": "alu",
+        "roofline": {"kernel": "region kernels (over the whole call)", "bound": "alu",
                      "achieved": round(tf, 2), "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(tf / FP64_PEAK_TFLOPS, 4), "traffic": None,
                      "algorithmic_gflop": round(flops / 1e9, 3), "avg_ms": round(avg, 5)},
@@ -600,7 +606,7 @@ def measure_route(args, workload):
                         "p90": round(pct(0.9), 5), "steps": n_prof,
                         "what": "profiled pass: stage events on the stream, after the timed steps"},
         "roofline": {
-            "kernel": "attn_sparse_kernel" if wl.dtype == "bf16" else "attn_f32_kernel",
+            "kernel": attention_kernel(p, wl.dtype),
             "bound": "hbm",
             "achieved": round(attn_gbs, 1),
             "peak": HBM_PEAK_GBS,
