@@ -289,7 +289,7 @@ mlp_score_kernel(const bf16_t* __restrict__ V, int N, int d, int B,
   load_w(0, wA);
   load_w(min(1, ksteps - 1), wB);
   wait_vmcnt<0>();
-  barrier_nofence();
+  barrier_lds();                                     // q_bar' and the first tiles are published
   hadamard_tile(0);
 
   // Step s: wait for the v tile of step s+1 (the Hadamard pass reads it),
@@ -301,8 +301,7 @@ mlp_score_kernel(const bf16_t* __restrict__ V, int N, int d, int B,
     // load, while there is one) and the W1 fragments of step s+1 (four loads)
     if (s + 2 < ksteps) wait_vmcnt<5>();
     else wait_vmcnt<4>();
-    wait_lgkm0();                                    // the wave's Hadamard chunks are written
-    barrier_nofence();
+    barrier_lds();                                   // (with the wave's Hadamard chunks)
     if (s + kMlpAhead < ksteps) issue_v(s + kMlpAhead);
     mma_step(s, w);
     if (s + 1 < ksteps) hadamard_tile(s + 1);

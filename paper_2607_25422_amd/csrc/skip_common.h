@@ -63,12 +63,18 @@ __device__ __forceinline__ void wait_lgkm0() {
   __builtin_amdgcn_s_waitcnt(0xC07F);
   asm volatile("" ::: "memory");
 }
-// Workgroup barrier without a memory fence: the waves that write LDS wait for
-// their own writes (vmcnt for direct loads, lgkmcnt for LDS stores) before it.
+// Workgroup barrier without a memory fence, for kernels whose LDS is written
+// by direct loads only: each wave waits for its own (wait_vmcnt) before it.
 __device__ __forceinline__ void barrier_nofence() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
+}
+// The same where waves also store to LDS: each waits for its own stores first,
+// so that the waves past the barrier read them.
+__device__ __forceinline__ void barrier_lds() {
+  wait_lgkm0();
+  barrier_nofence();
 }
 // A wave-uniform 64-bit value moved to scalar registers.
 __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
