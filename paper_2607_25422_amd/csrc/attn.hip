@@ -311,8 +311,7 @@ attn_sparse_kernel(const bf16_t* __restrict__ qbase, const int32_t* __restrict__
       auto step = [&](auto u, int i) {
         constexpr int sl = (decltype(u)::value + 2) % kSpRegTiles;
         if (i < n_tiles) {
-          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // tiles <= i+1 written
-          barrier_nofence();                                     // tile i is published
+          barrier_lds();                                         // tile i is published
           // (past the last tile a repeat, into a slot that is not read again)
           swrite(IntC<sl>{}, i + 2);
         }
@@ -590,7 +589,9 @@ attn_sparse_kernel(const bf16_t* __restrict__ qbase, const int32_t* __restrict__
       } else if (lk_phase < 2) {
         lookup_phase();
       }
-      barrier_nofence();               // tile i has landed
+      // tile i has landed, and every wave's merges of the passage before (the
+      // next passage's blocks hand rows to other waves)
+      barrier_lds();
       if (!busy) continue;
       const int stage = i % kSpStages;
       tile(IntC<0>{}, stage, cc.t, cc.te, first);

@@ -25,7 +25,8 @@ def kernel_body(source, name):
     return text[i:j]
 
 
-@pytest.mark.parametrize("source,name", [("mlp.hip", "mlp_score_kernel")])
+@pytest.mark.parametrize("source,name", [("mlp.hip", "mlp_score_kernel"),
+                                         ("attn.hip", "attn_sparse_kernel")])
 def test_kernels_that_store_to_lds_wait_for_their_stores(source, name):
     body = kernel_body(source, name)
     assert "barrier_lds()" in body
