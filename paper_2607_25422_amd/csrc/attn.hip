@@ -719,6 +719,15 @@ template <int D> struct TileOps<float, D> {
     const int hf = q >> 2, i = q & 3;
     return f32x4_t{acc[4 * hf][i], acc[4 * hf + 1][i], acc[4 * hf + 2][i], acc[4 * hf + 3][i]};
   }
+  __device__ static void set_piece(f32x4_t (&acc)[NA], int q, f32x4_t x) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[4 * (q >> 2) + u][q & 3] = x[u];
+  }
+  // the values of token(g, i) as zeros
+  __device__ static void clear_v(KV& x, int i) {
+#pragma unroll
+    for (int hf = 0; hf < NH; ++hf) x.v[NH * i + hf] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  }
 };
 
 // bfloat16: 32 tokens a block, v_mfma_f32_16x16x32_bf16.  S as in the sparse
@@ -786,6 +795,11 @@ template <int D> struct TileOps<bf16_t, D> {
     const int i = 4 * q / E, e = 4 * q % E;
     return f32x4_t{acc[e][i], acc[e + 1][i], acc[e + 2][i], acc[e + 3][i]};
   }
+  __device__ static void set_piece(f32x4_t (&acc)[NA], int q, f32x4_t x) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[4 * q % E + u][4 * q / E] = x[u];
+  }
+  __device__ static void clear_v(KV& x, int i) { x.v[i] = vword(0u); }
 };
 
 // Bound by the matrix cores at large batches (rows not adjacent to a passage
@@ -810,6 +824,25 @@ constexpr long long kTileWide = 1024;
 // question of 96 rows, 16 heads of 64: 44 against 59, 64 against 102 and 82
 // against 155.
 constexpr long long kTileWork = 768 * 64;
+
+// Whether an element of x is infinite or not a number, from the bits: at least
+// those of the infinity of its sign, as integers (opaque to the compiler: this
+// file is compiled for values that are numbers).
+template <int N>
+__device__ __forceinline__ bool any_not_finite(const f32x4_t (&x)[N]) {
+  int pos = 0;
+  uint32_t neg = 0u;
+#pragma unroll
+  for (int e = 0; e < N; ++e)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint32_t u = __float_as_uint(x[e][i]);
+      asm("" : "+v"(u));
+      pos = max(pos, (int)u);
+      neg = max(neg, u);
+    }
+  return pos >= 0x7f800000 || neg >= 0xff800000u;
+}
 
 template <typename T, int D, int NW>
 __global__ void __launch_bounds__(64 * NW, 2)
@@ -861,8 +894,8 @@ attn_tile_kernel(const T* __restrict__ qbase, const int32_t* __restrict__ kept_i
     int j, t, te;
   };
   // the wave's cursor: block nb of passage j (nbk blocks, tokens ts .. te - 1)
-  uint64_t rem = U;
-  int j = 0, ts = 0, te = 0, nb = wave, nbk = 0;
+  uint64_t rem;
+  int j = 0, ts = 0, te = 0, nb, nbk;
   auto load = [&](Block& x) -> bool {    // the next block of the wave, if any
     while (nb >= nbk) {
       if (!rem) return false;
@@ -882,11 +915,26 @@ attn_tile_kernel(const T* __restrict__ qbase, const int32_t* __restrict__ kept_i
     return true;
   };
 
+  // Rows not adjacent to a block's passage, and the tokens that pad its last
+  // block, meet V with a weight of 0.  That adds nothing as long as V is
+  // finite; if an accumulator ends infinite or not a number, the wave goes
+  // over its blocks again, `careful`: the accumulators of a row not adjacent to
+  // the passage are put back after the product, padding tokens count as zeros,
+  // and the weights stay <= 1, so that a value reaches only the rows with an
+  // edge to its passage and a sum overflows only where it must.
   f32x4_t acc[NA];
+  float m_run, l_run;                    // l_run: this lane's share of the row's sum
+  auto start = [&]() {
+    rem = U;
+    nb = wave;
+    nbk = 0;
+    m_run = -INFINITY;
+    l_run = 0.f;
 #pragma unroll
-  for (int e = 0; e < NA; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_run = 0.f;   // l_run: this lane's share of the row's sum
-  auto compute = [&](const Block& x) {
+    for (int e = 0; e < NA; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  };
+  auto compute = [&](Block& x, auto careful_) {
+    constexpr bool careful = decltype(careful_)::value != 0;
     float s[NS];
     Ops::logits(s, qf, x.kv);
     const bool adj = (mk >> x.j) & 1ull;
@@ -898,10 +946,11 @@ attn_tile_kernel(const T* __restrict__ qbase, const int32_t* __restrict__ kept_i
     }
     // the reference maximum moves when a logit exceeds it by more than kLazy
     // (weights stay <= 2^kLazy), so most blocks need no exchange or rescale
-    if (__any(lm > m_run + kLazy)) {
+    constexpr float slack = careful ? 0.f : kLazy;
+    if (__any(lm > m_run + slack)) {
       float mx = fmaxf(lm, swap16(lm));
       mx = fmaxf(mx, swap_halves(mx));
-      if (mx > m_run + kLazy) {
+      if (mx > m_run + slack) {
         const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - mx);
         m_run = mx;
         l_run *= alpha;
@@ -917,17 +966,34 @@ attn_tile_kernel(const T* __restrict__ qbase, const int32_t* __restrict__ kept_i
       ls += p[i];
     }
     l_run += ls;
+    if (careful) {
+#pragma unroll
+      for (int i = 0; i < NS; ++i)
+        if (x.t + Ops::token(g, i) >= x.te) Ops::clear_v(x.kv, i);
+#pragma unroll
+      for (int q = 0; q < Ops::kPieces; ++q)
+        *reinterpret_cast<f32x4_t*>(&po[wave][r16][Ops::first(g, q)]) = Ops::piece(acc, q);
+    }
     Ops::weigh(acc, x.kv, p);
+    if (careful && !adj)
+#pragma unroll
+      for (int q = 0; q < Ops::kPieces; ++q)
+        Ops::set_piece(acc, q, *reinterpret_cast<f32x4_t*>(&po[wave][r16][Ops::first(g, q)]));
   };
+  start();
   // two blocks in turn: one's loads are in flight while the other computes
   Block xa, xb;
   bool more = load(xa);
   while (more) {
     const bool second = load(xb);
-    compute(xa);
+    compute(xa, IntC<0>{});
     if (!second) break;
     more = load(xa);
-    compute(xb);
+    compute(xb, IntC<0>{});
+  }
+  if (__builtin_expect(__any(any_not_finite(acc)), 0)) {
+    start();
+    while (load(xa)) compute(xa, IntC<1>{});
   }
 
   // the waves' partials, merged in wave order

@@ -64,3 +64,75 @@ def test_attn_tile_edges(B, H, k, P, L_p, scale, d_h, dtype):
         assert batch.Vh.abs().max() < 5.5
         assert np.max(np.abs(O - O_ref)) <= 1.2e-4
     assert np.max(np.abs(L[live] - L_ref[live]) / np.maximum(1.0, np.abs(L_ref[live]))) <= 1e-5
+
+
+def run_given_graph(bnd, batch, Qh, adj, H, scale):
+    rp, col = [0], []
+    for row in (r for a in adj for r in a):
+        col.extend(np.nonzero(row)[0].tolist())
+        rp.append(len(col))
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device="cuda")  # noqa: E731
+    db = bnd.to_device(batch, sm_scale=scale, o_f32=True)
+    O, L, _, _ = bnd.bipartite_xattn(db, Qh.contiguous().cuda(), edges=(i32(rp), i32(col)))
+    return O.cpu().double().numpy(), L.cpu().double().numpy()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d_h", [64, 128])
+def test_attn_tile_values_reach_only_adjacent_rows(d_h, dtype):
+    """An infinity and a NaN among the values of two passages: rows without an
+    edge to them keep the result of finite values (the bars of the tile tests),
+    rows with one get the infinity (in the last token, which pads its block) or
+    the NaN, in that feature alone."""
+    from paper_2607_25422_amd import binding as bnd
+    H = 3
+    batch = wls.make_batch("tiny_fp32" if dtype == "f32" else "llava_bf16", 31, B=2, N=128, H=H,
+                           d_h=d_h, T=(4,), k=(33, 20), P=(5,), L_p=(5, 17, 300))
+    rng = np.random.default_rng(4)
+    adj = [rng.random((int(a), int(b))) < 0.4 for a, b in zip(batch.k, batch.P)]
+    Qh = torch.cat([batch.V[b, :int(n)] for b, n in enumerate(batch.k)]).view(-1, H, d_h)
+    if dtype == "bf16":
+        Qh = (Qh.float() * math.sqrt(H * d_h)).bfloat16()
+    _, _, O_ref, _ = orc.bipartite_xattn(
+        Qh, batch.kept_offsets, batch.Kh, batch.Vh, batch.passage_offsets,
+        batch.query_passages, 0.125, adjacency=adj)
+    ref = np.concatenate(O_ref)
+    at = batch.passage_offsets
+    Vh = batch.Vh.clone()
+    Vh[int(at[2]) - 1, 1, 3] = math.inf               # question 0, passage 1, its last token
+    Vh[int(at[5 + 3]), 2, d_h - 1] = math.nan         # question 1, passage 3, its first
+    batch.Vh = Vh
+    O, L = run_given_graph(bnd, batch, Qh, adj, H, 0.125)
+    k0 = int(batch.k[0])
+    inf_rows, nan_rows = np.nonzero(adj[0][:, 1])[0], k0 + np.nonzero(adj[1][:, 3])[0]
+    assert 0 < len(inf_rows) < k0 and 0 < len(nan_rows) < int(batch.k[1])
+    got = O[inf_rows, 1, 3]                           # (bf16: an infinity times a low part of 0 is no number)
+    assert np.all(got == math.inf) if dtype == "f32" else not np.isfinite(got).any()
+    assert np.all(np.isnan(O[nan_rows, 2, d_h - 1]))
+    O[inf_rows, 1, 3] = ref[inf_rows, 1, 3]
+    O[nan_rows, 2, d_h - 1] = ref[nan_rows, 2, d_h - 1]
+    if dtype == "f32":
+        rms = math.sqrt(np.mean(ref ** 2))
+        assert np.max(np.abs(O - ref) / np.maximum(np.abs(ref), rms)) <= 1e-5
+    else:
+        assert np.max(np.abs(O - ref)) <= 1.2e-4
+
+
+def test_attn_tile_large_values_do_not_overflow():
+    """A value of 3e37 under a weight that the softmax's reference maximum, as
+    the wave first meets it, would make 55: the weighted mean, 8.3e36, is far
+    inside the range."""
+    from paper_2607_25422_amd import binding as bnd
+    batch = wls.make_batch("tiny_fp32", 1, B=1, N=128, H=1, d_h=64, T=(4,), k=(17,), P=(1,),
+                           L_p=(144,))
+    Qh = torch.zeros(17, 1, 64)
+    Qh[:, 0, 0] = 1.0
+    batch.Kh = torch.zeros_like(batch.Kh)
+    batch.Vh = torch.zeros_like(batch.Vh)
+    batch.Kh[128, 0, 0] = 4.0                          # a later block of the first wave
+    batch.Vh[128, 0, 5] = 3e37
+    O, _ = run_given_graph(bnd, batch, Qh, [np.ones((17, 1), dtype=bool)], 1, 1.0)
+    want = 3e37 * math.exp(4.0) / (143 + math.exp(4.0))
+    assert np.all(np.abs(O[:, 0, 5] / want - 1) <= 1e-5)
+    O[:, 0, 5] = 0
+    assert np.all(O == 0)
