@@ -10,6 +10,8 @@
 //
 // fp32 inputs and small bf16 problems: 16 rows per workgroup, token blocks
 // split over its waves (at that kernel).
+#include <algorithm>
+
 #include "skip_common.h"
 #include "skip_internal.h"
 #include "skip_plan.h"
@@ -844,6 +846,10 @@ __device__ __forceinline__ bool any_not_finite(const f32x4_t (&x)[N]) {
   return pos >= 0x7f800000 || neg >= 0xff800000u;
 }
 
+// Workgroups of a row of the grid: a dimension of a launch takes fewer than 2^32
+// threads, 2^23 workgroups of 512.
+constexpr int kTileGridX = 1 << 22;
+
 template <typename T, int D, int NW>
 __global__ void __launch_bounds__(64 * NW, 2)
 attn_tile_kernel(const T* __restrict__ qbase, const int32_t* __restrict__ kept_idx, int N,
@@ -851,8 +857,8 @@ attn_tile_kernel(const T* __restrict__ qbase, const int32_t* __restrict__ kept_i
                  const T* __restrict__ Kh, const T* __restrict__ Vh,
                  const int32_t* __restrict__ passage_offsets,
                  const int32_t* __restrict__ query_passages,
-                 const uint64_t* __restrict__ rowmask, int H, int groups, int tiles,
-                 int total_kept, int total_passages, int total_tokens, int k_max, int P_max,
+                 const uint64_t* __restrict__ rowmask, int H, int groups, int ygroups,
+                 int tiles, int total_kept, int total_passages, int total_tokens, int k_max, int P_max,
                  float scale_log2, void* __restrict__ O, int o_f32, float* __restrict__ lse) {
   using Ops = TileOps<T, D>;
   constexpr int TB = Ops::kTok, NS = Ops::kS, NA = Ops::NA;
@@ -860,8 +866,9 @@ attn_tile_kernel(const T* __restrict__ qbase, const int32_t* __restrict__ kept_i
   __shared__ __align__(16) float po[NW][kTileRows][OS];
   __shared__ float pm[NW][kTileRows], pl[NW][kTileRows];
   // all row tiles of a (question, head) on one XCD (workgroup id L goes to
-  // XCD L % 8), where they share its K and V in the L2
-  const int L = blockIdx.x, grp = (L & 7) + 8 * ((L >> 3) / tiles);
+  // XCD L % 8), where they share its K and V in the L2; blockIdx.y: ygroups
+  // (question, head) pairs each
+  const int L = blockIdx.x, grp = blockIdx.y * ygroups + (L & 7) + 8 * ((L >> 3) / tiles);
   if (grp >= groups) return;
   const int b = grp / H, h = grp % H, r0 = ((L >> 3) % tiles) * kTileRows;
   int k0, k1, p0, p1;
@@ -1086,14 +1093,18 @@ hipError_t launch_attention(const skip_problem_t& p, QuerySource q,
 #undef SKIP_ATTN_SPARSE
   } else {
     const long long groups = (long long)p.B * p.H;
+    if (groups > INT32_MAX - kTileGridX) return hipErrorInvalidValue;
     const int tiles = (p.k_max + kTileRows - 1) / kTileRows;
     const long long nwg = 8 * ((groups + 7) / 8) * tiles;
-    if (nwg > INT32_MAX / 512) return hipErrorInvalidValue;
+    // one row of the grid, as a rule
+    const int ygroups = (int)std::min<long long>(8 * ((groups + 7) / 8),
+                                                 std::max(8, kTileGridX / tiles / 8 * 8));
+    const dim3 grid(ygroups * tiles, (unsigned)((groups + ygroups - 1) / ygroups));
 #define SKIP_ATTN_TILE(T, DD, NW)                                                            \
-  hipLaunchKernelGGL((attn_tile_kernel<T, DD, NW>), dim3((unsigned)nwg), dim3(64 * NW), 0,   \
-                     s, (const T*)q.base, q.kept_idx, q.N, qstride, kept_offsets,            \
+  hipLaunchKernelGGL((attn_tile_kernel<T, DD, NW>), grid, dim3(64 * NW), 0, s,               \
+                     (const T*)q.base, q.kept_idx, q.N, qstride, kept_offsets,               \
                      (const T*)Kh, (const T*)Vh, passage_offsets, query_passages, rowmask,   \
-                     p.H, (int)groups, tiles, p.total_kept, p.total_passages,                \
+                     p.H, (int)groups, ygroups, tiles, p.total_kept, p.total_passages,       \
                      p.total_tokens, p.k_max, p.P_max, p.sm_scale * kLog2e, O,               \
                      p.dtype == SKIP_F32 || p.o_f32, lse)
     const bool wide = nwg >= kTileWide;

@@ -136,3 +136,37 @@ def test_attn_tile_large_values_do_not_overflow():
     assert np.all(np.abs(O[:, 0, 5] / want - 1) <= 1e-5)
     O[:, 0, 5] = 0
     assert np.all(O == 0)
+
+
+def test_attn_tile_more_workgroups_than_a_row_of_the_grid():
+    """33 000 questions of one row and 128 heads make 4.2 million workgroups,
+    more than one dimension of a launch holds: the last question of the first
+    row of the grid and the ones beside it, the first and the last have a
+    passage of one token, whose value is their result; the others have none."""
+    from paper_2607_25422_amd import binding as bnd
+    B, H, d_h = 33000, 128, 64
+    at = [0, 2 ** 15 - 1, 2 ** 15, B - 1]             # 2^22 workgroups a row: 2^15 questions
+    P = np.zeros(B, dtype=np.int64)
+    P[at] = 1
+    offs = dict(q_offsets=np.arange(B + 1), kept_offsets=np.arange(B + 1),
+                passage_offsets=np.arange(len(at) + 1),
+                query_passages=np.concatenate([[0], np.cumsum(P)]))
+    offs = {n: a.astype(np.int32) for n, a in offs.items()}
+    p = bnd.make_problem("f32", B=B, N=1, d=H * d_h, H=H, d_h=d_h, avg_degree=1.0, sm_scale=0.125,
+                         o_f32=True, edge_rule="question", edge_metric="cosine", **offs)
+    dev = {n: torch.from_numpy(a).cuda() for n, a in offs.items()}
+    g = torch.Generator(device="cuda").manual_seed(1)
+    Kh, Vh = (torch.randn(len(at), H, d_h, generator=g, device="cuda") for _ in range(2))
+    Qh = torch.ones(B, H, d_h, device="cuda")
+    db = bnd.DeviceBatch(p=p, V=Qh.view(B, 1, -1), Qtok=Qh.view(B, -1), q_offsets=dev["q_offsets"],
+                         kept_offsets=dev["kept_offsets"], Kh=Kh, Vh=Vh,
+                         passage_offsets=dev["passage_offsets"],
+                         query_passages=dev["query_passages"], w_bias=None,
+                         workspace=bnd.new_workspace(p, "cuda"))
+    edges = (dev["query_passages"], torch.zeros(len(at), dtype=torch.int32, device="cuda"))
+    O, L, _, _ = bnd.bipartite_xattn(db, Qh, edges=edges)
+    assert torch.equal(O[at], Vh)
+    want = 0.125 * Kh.double().sum(2)
+    assert float((L[at].double() - want).abs().max()) <= 1e-5 * (1 + float(want.abs().max()))
+    O[at] = 0
+    assert not bool(O.any()) and int(torch.isneginf(L).sum()) == (B - len(at)) * H
