@@ -819,13 +819,22 @@ constexpr long long kTileWide = 1024;
 // bf16 problems of at most this many workgroups x d_h go by row tiles, larger
 // ones to the sparse kernel, whose items of up to 192 rows read K and V once
 // but leave most of the chip idle at few (question, head) pairs and walk the
-// passages one tile of tokens after the other.  Routes, tiles against sparse
-// (5 x 128, 10 x 256 and 20 x 256 tokens, 48 to 384 rows): at 768 workgroups
-// of d_h = 64 59-145 us against 66-163, at 1536 75-230 against 77-167; at 384
-// of d_h = 128 68-184 against 88-192, at 768 84-226 against 80-205; one
-// question of 96 rows, 16 heads of 64: 44 against 59, 64 against 102 and 82
-// against 155.
+// passages one tile of tokens after the other.  A tile computes every passage
+// adjacent to one of its rows; with many passages and few edges that is more
+// work, but the sparse kernel's items walk as many.  Graph and attention call,
+// 16 heads of 64, 96 rows, tiles against sparse: 8 questions (768 workgroups),
+// 5 passages of 128 tokens and degree 4 40 us against 47, 20 of 256 140 against
+// 146, 64 of 128 175 against 259 (degree 1: 119 against 212); one question, 64
+// of 512 191 against 627.  At 1536 workgroups routes take 75-230 us against
+// 77-167.
+// Long passages cost the tiles more, as each streams K and V again: past 256
+// tokens 768 workgroups lose up to 14 % (20 of 1024 tokens, degree 2: 488 us
+// against 421; 5 of 512 86 against 83), 576 break even (81-451 against 83-417)
+// and 480 win from 14 % up (72-336 against 83-417), the same at half the
+// workgroups of d_h = 128: hence kTileWorkLong.
 constexpr long long kTileWork = 768 * 64;
+constexpr long long kTileWorkLong = 512 * 64;
+constexpr int kTileLong = 256;         // longest passage, in tokens, that kTileWork holds for
 
 // Whether an element of x is infinite or not a number, from the bits: at least
 // those of the infinity of its sign, as integers (opaque to the compiler: this
@@ -1046,7 +1055,8 @@ attn_tile_kernel(const T* __restrict__ qbase, const int32_t* __restrict__ kept_i
 // Whether the row-tile kernel runs (else the passage-major sparse kernel).
 bool attn_by_tiles(const skip_problem_t& p) {
   if (p.dtype != SKIP_BF16) return true;
-  return (long long)p.B * p.H * ((p.k_max + kTileRows - 1) / kTileRows) * p.d_h <= kTileWork;
+  return (long long)p.B * p.H * ((p.k_max + kTileRows - 1) / kTileRows) * p.d_h <=
+         (p.L_max <= kTileLong ? kTileWork : kTileWorkLong);
 }
 
 long long attn_plan_ids(const skip_problem_t& p) {

@@ -31,6 +31,8 @@ pytestmark = pytest.mark.gpu
     (12, 16, (47, 64), (5,), (31, 64), 0.125),          # 768 workgroups: the bf16 rule's line
     (13, 16, (47, 64), (5,), (31, 64), 0.125),          # past it
     (40, 8, (47, 64), (4, 5), (1, 31, 48), 0.125),      # 1280 workgroups: four waves each (f32)
+    (8, 16, (47, 64), (3,), (257, 31), 0.125),          # 512 workgroups: the rule's line past 256 tokens
+    (9, 16, (47, 64), (3,), (257, 31), 0.125),          # past it
 ])
 def test_attn_tile_edges(B, H, k, P, L_p, scale, d_h, dtype):
     from paper_2607_25422_amd import binding as bnd

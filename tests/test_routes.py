@@ -1,0 +1,41 @@
+"""Which kernel a problem goes to, asked of the library's own rules (host code:
+no GPU is needed)."""
+import ctypes
+
+import pytest
+
+from paper_2607_25422_amd import binding as B
+
+
+def problem(dtype="bf16", **kw):
+    p = B.SkipProblem()
+    p.dtype = B.SKIP_F32 if dtype == "f32" else B.SKIP_BF16
+    for n, v in {**dict(B=1, N=4096, H=16, d_h=64, k_max=96, P_max=5, L_max=128), **kw}.items():
+        setattr(p, n, v)
+    p.d = p.H * p.d_h
+    p.total_kept, p.total_passages = p.B * p.k_max, p.B * p.P_max
+    p.total_tokens = p.total_passages * p.L_max
+    return p
+
+
+def by_tiles(p):
+    f = B.LIB["_ZN4skip13attn_by_tilesERK12skip_problem"]
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.POINTER(B.SkipProblem)]
+    return f(ctypes.byref(p))
+
+
+@pytest.mark.parametrize("want,kw", [
+    (True, dict(B=8)),                               # 768 workgroups of d_h = 64
+    (False, dict(B=9)),
+    (True, dict(B=4, d_h=128)),                      # half of them at 128
+    (False, dict(B=5, d_h=128)),
+    (True, dict(B=8, L_max=256)),                    # long passages: two thirds of them
+    (False, dict(B=8, L_max=257)),
+    (True, dict(B=5, L_max=1024)),
+    (False, dict(B=6, L_max=1024, P_max=20)),        # 451 us by tiles, 417 without
+    (False, dict(B=4, d_h=128, L_max=512)),
+    (True, dict(B=1, k_max=192, P_max=64, L_max=512)),
+    (True, dict(B=64, L_max=1024, dtype="f32")),     # float32 always
+])
+def test_row_tiles_take_small_bf16_problems(want, kw):
+    assert by_tiles(problem(**kw)) is want
