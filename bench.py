@@ -128,10 +128,17 @@ def measure_ceilings(torch) -> dict:
                     "16384^3 bf16 GEMM (torch.matmul)"}
 
 
-def attention_kernel(p, dtype):
-    """Name of the kernel that runs the attention (the rule of the library)."""
-    tiles = p.B * p.H * ((p.k_max + 15) // 16) * p.d_h <= 768 * 64
-    return "attn_tile_kernel" if dtype != "bf16" or tiles else "attn_sparse_kernel"
+def attention_kernel(p):
+    """(name, bound) of the kernel that runs the attention, by the library's
+    own rule (skip::attn_by_tiles)."""
+    import ctypes
+
+    from paper_2607_25422_amd import binding as B
+    by_tiles = B.LIB["_ZN4skip13attn_by_tilesERK12skip_problem"]
+    by_tiles.restype = ctypes.c_bool
+    if by_tiles(ctypes.byref(p)):
+        return "attn_tile_kernel", "latency"
+    return "attn_sparse_kernel", "hbm"
 
 
 def measured_traffic(workload: str):
@@ -580,6 +587,7 @@ def measure_route(args, workload):
     torch.cuda.synchronize()
     prune_ms = sorted(a.elapsed_time(b) for a, b in pev)[n_prof // 2]
     score_gbs = score_bytes / (prune_ms * 1e-3) / 1e9
+    kernel, bound = attention_kernel(p)
 
     res = {
         "metric": METRIC,
@@ -606,8 +614,8 @@ def measure_route(args, workload):
                         "p90": round(pct(0.9), 5), "steps": n_prof,
                         "what": "profiled pass: stage events on the stream, after the timed steps"},
         "roofline": {
-            "kernel": attention_kernel(p, wl.dtype),
-            "bound": "hbm",
+            "kernel": kernel,
+            "bound": bound,
             "achieved": round(attn_gbs, 1),
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",

@@ -39,3 +39,10 @@ def by_tiles(p):
 ])
 def test_row_tiles_take_small_bf16_problems(want, kw):
     assert by_tiles(problem(**kw)) is want
+
+
+def test_the_benchmark_names_the_kernel_by_the_same_rule():
+    import bench
+    for kw in (dict(B=8), dict(B=9), dict(B=8, L_max=257), dict(B=64, dtype="f32")):
+        name = bench.attention_kernel(problem(**kw))[0]
+        assert name == ("attn_tile_kernel" if by_tiles(problem(**kw)) else "attn_sparse_kernel")
