@@ -619,15 +619,10 @@ region_step_kernel(const T* __restrict__ rows, RegionArgs a) {
 //   region_mean_kernel     the centroids: means over each region's last rows
 //                          (its start row if it never had any)
 // Measured against a step launch per iteration (16 questions of 192 rows, d =
-// 4096, R = 8, 10 iterations): 63 + 74 + 14 us, the call 147 us against 310;
-// 96 rows of d = 1024: 71 against 235.  The products grow with the square of
-// the rows: at 384 rows 432 us against 578 (bf16) and 529 against 677
-// (float32), at 512 743 against 777 and 905 against 830, hence the limit; and
-// they do not shrink with the iterations, hence kGramRowsPerIter (10
-// iterations reach the limit).
+// 4096, R = 8, 10 iterations): the call 147 us against 310; 96 rows of d = 1024:
+// 71 against 235.  Where it is taken: regions_by_gram.
 constexpr int kGramTile = 16;
 constexpr int kGramMaxRows = 384;        // rows per question
-constexpr int kGramRowsPerIter = 38;     // rows per question and iteration
 constexpr int kGramThreads = 1024;
 constexpr int kGramWaves = kGramThreads / 64;
 constexpr int kGramWords = kGramMaxRows / 64;
@@ -955,10 +950,45 @@ static size_t ralign(size_t n) { return (n + 255) & ~(size_t)255; }
 
 static int gram_ld(const skip_problem_t& p) { return (p.k_max + 15) / 16 * 16; }
 
-// Whether the iterations may run on the Gram matrix, and whether they do.
 static bool gram_shape(const skip_problem_t& p) { return p.k_max <= kGramMaxRows; }
-static bool regions_by_gram(const skip_problem_t& p, int n_iter) {
-  return gram_shape(p) && p.k_max <= (long long)kGramRowsPerIter * n_iter;
+
+// Whether the iterations run on the Gram matrix.  Its products cost the square
+// of the rows, once; a step costs about the rows and grows with the region
+// bound it is compiled for (4, 8, 16).  While the chip is not filled both are
+// bound by latency, and the line is 38.4 rows an iteration: 384 rows at ten (432
+// us against 578 at d = 4096, 529 against 677 in float32; 512 rows: 743 against
+// 777 and 905 against 830).  That holds for any number of questions where their
+// column slices make the step launch several rounds of workgroups, one a CU
+// (Gram over step time at most 0.95, mostly 0.3-0.8).  Where it makes one round:
+//   * R <= 4 from 49 questions on: 1.08 at the line, 1.02 at 33 rows;
+//   * one or two slices (d <= 512), many questions: every question's
+//     iterations read its part of G from the L2s or the cache behind them, so
+//     fewer rows pay.  65 .. 128 questions: up to 1.32, 1.09 and 0.75 (R <= 4,
+//     8, 16) at the line, 1.02, 0.98 and 0.75 at the rows taken; more: up to
+//     2.37, 1.87 and 1.29, and 1.00, 1.01 and 0.99 at rows whose square is
+//     bound (20 iterations and more are alike).
+// Up to 64 rows, one block of a wave, none of these lose (at most 0.93).  One
+// iteration is two steps, and on few questions of long rows those are faster
+// than the three launches of this form (d = 4096, 24 rows: 28 us against 31; R >
+// 4, in float32 R > 8, no longer).
+bool regions_by_gram(const skip_problem_t& p, int r_max, int n_iter) {
+  const int S = region_slices(p);
+  const int c = r_max <= 4 ? 0 : (r_max <= 8 ? 1 : 2);
+  if (!gram_shape(p)) return false;
+  if (n_iter == 1 && S > 8 && p.B <= 16 && c < (p.dtype == SKIP_F32 ? 2 : 1)) return false;
+  const long long k = p.k_max;
+  int per10 = 384;                                       // rows per ten iterations
+  if (k <= 64) {
+  } else if (S > 2) {
+    if (c == 0 && p.B > 48 && (long long)p.B * S <= 256) per10 = 330;
+  } else if (p.B > 128) {
+    constexpr int square[3] = {1900, 3300, 7400};        // rows^2 per iteration
+    if (k * k > (long long)square[c] * std::min(n_iter, 20)) return false;
+  } else if (p.B > 64) {
+    constexpr int rows[3] = {300, 360, 384};
+    per10 = rows[c];
+  }
+  return k * 10 <= (long long)per10 * n_iter;
 }
 
 static size_t gram_scratch_bytes(const skip_problem_t& p) {
@@ -1016,7 +1046,7 @@ hipError_t launch_regions(const skip_problem_t& p, const void* rows, const int32
                           float* centroids, int32_t* sizes, void* scratch, hipStream_t s) {
   const int S = region_slices(p);
   char* c = static_cast<char*>(scratch);
-  if (regions_by_gram(p, n_iter)) {
+  if (regions_by_gram(p, r_max, n_iter)) {
     RegionGramArgs g;
     g.kept_offsets = kept_offsets;
     g.kept_idx = kept_idx;

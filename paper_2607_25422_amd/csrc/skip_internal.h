@@ -100,6 +100,8 @@ hipError_t launch_project(const skip_problem_t& p, const void* rows, const int32
 // Regions of the kept tokens (k-means) ------------------------------------
 int region_slices(const skip_problem_t& p);
 size_t region_scratch_bytes(const skip_problem_t& p, int r_max);
+// whether the iterations run on the Gram matrix (else a launch per step)
+bool regions_by_gram(const skip_problem_t& p, int r_max, int n_iter);
 // rows: the kept rows (kept_idx NULL) or V read through kept_idx
 hipError_t launch_regions(const skip_problem_t& p, const void* rows, const int32_t* kept_offsets,
                           const int32_t* kept_idx, int r_max, int n_iter, int32_t* region,

@@ -134,6 +134,10 @@ def test_regions_full_size(B):
     ("llava_bf16", 5, 64, (63, 64, 65, 97), 8, 7),
     ("llava_bf16", 3, 64, (383, 384), 16, 11),            # the largest Gram matrix
     ("llava_bf16", 3, 64, (384, 385), 16, 11),            # past it
+    ("llava_bf16", 3, 64, (381, 384), 8, 10),             # the largest at ten iterations
+    ("llava_bf16", 32, 128, (33, 7), 4, 1),               # one iteration of long rows: steps, 16 slices
+    ("tiny_fp32", 32, 128, (385, 64), 8, 3),              # steps of 16 slices
+    ("llava_bf16", 32, 128, (385, 64), 16, 3),
 ])
 def test_regions_gram_edges(B, wl, H, d_h, k, r_max, n_iter):
     """Both sides of the rule that takes small questions to the Gram matrix,

@@ -41,6 +41,40 @@ def test_row_tiles_take_small_bf16_problems(want, kw):
     assert by_tiles(problem(**kw)) is want
 
 
+def by_gram(p, r_max, n_iter):
+    f = B.LIB["_ZN4skip15regions_by_gramERK12skip_problemii"]
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.POINTER(B.SkipProblem), ctypes.c_int,
+                                            ctypes.c_int]
+    return f(ctypes.byref(p), r_max, n_iter)
+
+
+@pytest.mark.parametrize("want,B,k,H,r_max,n_iter", [
+    (True, 4, 384, 64, 8, 10),                       # d = 4096: the largest, at ten iterations
+    (False, 4, 385, 64, 8, 100),
+    (True, 16, 38, 16, 16, 1),
+    (False, 16, 39, 16, 16, 1),
+    (True, 1, 33, 32, 4, 1),                         # one iteration: up to d = 2048
+    (False, 1, 33, 64, 4, 1),
+    (True, 64, 16, 64, 4, 1),                        # or many questions
+    (True, 48, 384, 16, 4, 10),
+    (True, 64, 330, 16, 4, 10),                      # one round of step workgroups, R <= 4
+    (False, 64, 331, 16, 4, 10),
+    (False, 64, 190, 16, 4, 5),
+    (True, 64, 384, 16, 8, 10),
+    (True, 64, 384, 8, 4, 10),
+    (True, 65, 384, 16, 4, 10),                      # more than a round
+    (False, 128, 301, 4, 4, 10),                     # d <= 512, 65 .. 128 questions
+    (False, 128, 361, 8, 8, 10),
+    (True, 128, 384, 4, 16, 10),
+    (False, 256, 190, 4, 4, 5),                      # more: 2.1 times the step launches
+    (True, 256, 97, 4, 4, 5),
+    (False, 256, 384, 4, 8, 1000),
+    (True, 256, 192, 64, 4, 10),
+])
+def test_regions_on_the_gram_matrix(want, B, k, H, r_max, n_iter):
+    assert by_gram(problem(B=B, k_max=k, H=H), r_max, n_iter) is want
+
+
 def test_the_benchmark_names_the_kernel_by_the_same_rule():
     import bench
     for kw in (dict(B=8), dict(B=9), dict(B=8, L_max=257), dict(B=64, dtype="f32")):
