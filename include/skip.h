@@ -366,7 +366,10 @@ skip_status_t skip_gather_project_packed(const skip_problem_t* p, const void* ro
  *             iteration, rounded to float (rows r >= R_b are 0)
  *   sizes     out [B][r_max] int32 rows per region, or NULL
  * Distances are compared as |c_r|^2 - 2 v.c_r (the row's own |v|^2 is common
- * to all regions).  Workspace: skip_workspace_bytes_regions.
+ * to all regions).  Workspace: skip_workspace_bytes_regions, which for small
+ * questions includes [B][k_max][k_max] double (k_max rounded up to 16) for the
+ * products of their rows; without that part the call takes the slower form of
+ * a launch per iteration, whose centroids may differ in their last bits.
  */
 skip_status_t skip_workspace_bytes_regions(const skip_problem_t* p, int32_t r_max,
                                            size_t* bytes);

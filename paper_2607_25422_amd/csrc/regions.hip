@@ -28,6 +28,7 @@ namespace skip {
 constexpr int kRegCols = 256;     // columns per slice = threads per workgroup
 constexpr int kRegMax = 16;       // largest r_max
 constexpr int kRegMaxRows = 16384; // largest k_max
+constexpr int kRegMaxIter = 1000; // largest n_iter
 
 namespace {
 
@@ -1017,17 +1018,21 @@ static hipError_t launch_gram(const skip_problem_t& p, const T* rows, const Regi
 
 int region_slices(const skip_problem_t& p) { return (p.d + kRegCols - 1) / kRegCols; }
 
-size_t region_scratch_bytes(const skip_problem_t& p, int r_max) {
+size_t region_least_bytes(const skip_problem_t& p, int r_max) {
   const size_t S = (size_t)region_slices(p);
-  const size_t gram = gram_shape(p) ? gram_scratch_bytes(p) : 0;
-  const size_t steps = ralign((size_t)p.B * r_max * p.d * sizeof(double)) +
+  return ralign((size_t)p.B * r_max * p.d * sizeof(double)) +
          ralign((size_t)p.B * S * (p.k_max + 1) * r_max * sizeof(double)) +
          ralign((size_t)p.total_kept) +
          ralign((size_t)p.total_kept * sizeof(int32_t)) +
          ralign((size_t)p.total_kept) +
          ralign((size_t)p.B * r_max * sizeof(int32_t)) +
          ralign((size_t)p.B * sizeof(int32_t));
-  return std::max(gram, steps);
+}
+
+// (the Gram matrix's as well, if some number of iterations takes it)
+size_t region_scratch_bytes(const skip_problem_t& p, int r_max) {
+  const size_t steps = region_least_bytes(p, r_max);
+  return regions_by_gram(p, r_max, kRegMaxIter) ? std::max(steps, gram_scratch_bytes(p)) : steps;
 }
 
 template <typename T, bool IDX>
@@ -1043,10 +1048,11 @@ static void launch_step(int r_max, dim3 grid, dim3 block, hipStream_t s, const T
 
 hipError_t launch_regions(const skip_problem_t& p, const void* rows, const int32_t* kept_offsets,
                           const int32_t* kept_idx, int r_max, int n_iter, int32_t* region,
-                          float* centroids, int32_t* sizes, void* scratch, hipStream_t s) {
+                          float* centroids, int32_t* sizes, void* scratch, size_t scratch_bytes,
+                          hipStream_t s) {
   const int S = region_slices(p);
   char* c = static_cast<char*>(scratch);
-  if (regions_by_gram(p, r_max, n_iter)) {
+  if (regions_by_gram(p, r_max, n_iter) && scratch_bytes >= gram_scratch_bytes(p)) {
     RegionGramArgs g;
     g.kept_offsets = kept_offsets;
     g.kept_idx = kept_idx;

@@ -694,10 +694,10 @@ skip_status_t skip_region_kmeans(const skip_problem_t* p, const void* rows,
     if (p->N < 1 || p->k_max > p->N) return SKIP_ERR_INVALID_ARG;
     if ((int64_t)p->B * p->N > INT32_MAX) return SKIP_ERR_UNSUPPORTED;
   }
-  if (workspace_bytes < region_scratch_bytes(*p, r_max)) return SKIP_ERR_WORKSPACE;
+  if (workspace_bytes < region_least_bytes(*p, r_max)) return SKIP_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   SKIP_TRY(launch_regions(*p, rows, kept_offsets, kept_idx, r_max, n_iter, region, centroids,
-                          sizes, workspace, s));
+                          sizes, workspace, workspace_bytes, s));
   return SKIP_OK;
 }
 

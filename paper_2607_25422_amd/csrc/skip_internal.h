@@ -100,12 +100,14 @@ hipError_t launch_project(const skip_problem_t& p, const void* rows, const int32
 // Regions of the kept tokens (k-means) ------------------------------------
 int region_slices(const skip_problem_t& p);
 size_t region_scratch_bytes(const skip_problem_t& p, int r_max);
+size_t region_least_bytes(const skip_problem_t& p, int r_max);   // enough for a launch per step
 // whether the iterations run on the Gram matrix (else a launch per step)
 bool regions_by_gram(const skip_problem_t& p, int r_max, int n_iter);
 // rows: the kept rows (kept_idx NULL) or V read through kept_idx
 hipError_t launch_regions(const skip_problem_t& p, const void* rows, const int32_t* kept_offsets,
                           const int32_t* kept_idx, int r_max, int n_iter, int32_t* region,
-                          float* centroids, int32_t* sizes, void* scratch, hipStream_t s);
+                          float* centroids, int32_t* sizes, void* scratch, size_t scratch_bytes,
+                          hipStream_t s);
 
 // Stage 2 ---------------------------------------------------------------
 // Query rows: if kept_idx is non-NULL, row r of question b is

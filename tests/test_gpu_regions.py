@@ -160,3 +160,25 @@ def test_regions_gram_edges(B, wl, H, d_h, k, r_max, n_iter):
     if n_iter == 1:
         n, R = int(batch.k[0]), orc.region_count(int(batch.k[0]), r_max)
         assert R < 3 or int(out[2][0, 2]) == 0
+
+
+def test_regions_workspace_of_the_step_form(B):
+    """A workspace without room for the Gram matrix, the size that the step form
+    needs, takes the step form; one byte less is refused."""
+    batch = wls.make_batch("llava_bf16", 17, B=4, N=400, H=2, d_h=64, T=(2,), k=(300, 291))
+    kept = [np.arange(int(n), dtype=np.int64) + 3 for n in batch.k]
+    db = B.to_device(batch)
+    p, r_max, n_iter = db.p, 8, 10
+    al = lambda n: (n + 255) // 256 * 256  # noqa: E731
+    S = (p.d + 255) // 256
+    least = (al(p.B * r_max * p.d * 8) + al(p.B * S * (p.k_max + 1) * r_max * 8) +
+             2 * al(p.total_kept) + al(p.total_kept * 4) + al(p.B * r_max * 4) + al(p.B * 4))
+    assert B.workspace_bytes_regions(p, r_max) == al(p.B * 304 * 304 * 8) + al(p.B * 16 * 6 * 8) > least
+    idx = torch.from_numpy(np.concatenate(kept).astype(np.int32)).cuda()
+    for size in (least, B.workspace_bytes_regions(p, r_max) - 1):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        out = B.region_kmeans(db, db.V, kept_idx=idx, r_max=r_max, n_iter=n_iter, workspace=ws)
+        check_regions(batch, kept, *out, r_max, n_iter, f"{size} bytes")
+    with pytest.raises(B.SkipError):
+        B.region_kmeans(db, db.V, kept_idx=idx, r_max=r_max, n_iter=n_iter,
+                        workspace=torch.empty(least - 1, dtype=torch.uint8, device="cuda"))
