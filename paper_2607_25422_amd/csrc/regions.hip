@@ -953,6 +953,19 @@ static int gram_ld(const skip_problem_t& p) { return (p.k_max + 15) / 16 * 16; }
 
 static bool gram_shape(const skip_problem_t& p) { return p.k_max <= kGramMaxRows; }
 
+// Tiles of the lower triangles, and workgroups of the product launch: below
+// 2^24 of 256 threads (2^32 threads in a dimension), questions below 2^16 (the
+// second dimension of the means).
+constexpr int kGramMaxBatch = 65535;
+constexpr long long kGramMaxGrid = (1 << 24) - 1;
+static int gram_pairs(const skip_problem_t& p) {
+  const int nt = (p.k_max + kGramTile - 1) / kGramTile;
+  return nt * (nt + 1) / 2;
+}
+static long long gram_grid(const skip_problem_t& p) {
+  return 8ll * ((p.B + 7ll) / 8) * gram_pairs(p);
+}
+
 // Whether the iterations run on the Gram matrix.  Its products cost the square
 // of the rows, once; a step costs about the rows and grows with the region
 // bound it is compiled for (4, 8, 16).  While the chip is not filled both are
@@ -971,11 +984,12 @@ static bool gram_shape(const skip_problem_t& p) { return p.k_max <= kGramMaxRows
 // Up to 64 rows, one block of a wave, none of these lose (at most 0.93).  One
 // iteration is two steps, and on few questions of long rows those are faster
 // than the three launches of this form (d = 4096, 24 rows: 28 us against 31; R >
-// 4, in float32 R > 8, no longer).
+// 4, in float32 R > 8, no longer).  Batches past a grid's dimensions take the
+// step form, whose grid holds more.
 bool regions_by_gram(const skip_problem_t& p, int r_max, int n_iter) {
   const int S = region_slices(p);
   const int c = r_max <= 4 ? 0 : (r_max <= 8 ? 1 : 2);
-  if (!gram_shape(p)) return false;
+  if (!gram_shape(p) || p.B > kGramMaxBatch || gram_grid(p) > kGramMaxGrid) return false;
   if (n_iter == 1 && S > 8 && p.B <= 16 && c < (p.dtype == SKIP_F32 ? 2 : 1)) return false;
   const long long k = p.k_max;
   int per10 = 384;                                       // rows per ten iterations
@@ -1001,11 +1015,8 @@ template <typename T, bool IDX>
 static hipError_t launch_gram(const skip_problem_t& p, const T* rows, const RegionGramArgs& a,
                               hipStream_t s) {
   if (p.k_max > 0) {
-    const int nt = (p.k_max + kGramTile - 1) / kGramTile, pairs = nt * (nt + 1) / 2;
-    const long long grid = 8ll * ((p.B + 7) / 8) * pairs;
-    if (grid > INT32_MAX) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((region_gram_kernel<T, IDX>), dim3((unsigned)grid), dim3(256), 0, s, rows,
-                       a, pairs);
+    hipLaunchKernelGGL((region_gram_kernel<T, IDX>), dim3((unsigned)gram_grid(p)), dim3(256), 0,
+                       s, rows, a, gram_pairs(p));
   }
   const dim3 grid(p.B), block(kGramThreads);
   if (a.r_max <= 4) hipLaunchKernelGGL(region_iterate_kernel<4>, grid, block, 0, s, a);

@@ -70,6 +70,10 @@ def by_gram(p, r_max, n_iter):
     (True, 256, 97, 4, 4, 5),
     (False, 256, 384, 4, 8, 1000),
     (True, 256, 192, 64, 4, 10),
+    (True, 65535, 16, 16, 8, 10),                    # the grids' dimensions
+    (False, 65536, 16, 16, 8, 10),
+    (True, 55920, 384, 16, 16, 10),
+    (False, 55928, 384, 16, 16, 10),
 ])
 def test_regions_on_the_gram_matrix(want, B, k, H, r_max, n_iter):
     assert by_gram(problem(B=B, k_max=k, H=H), r_max, n_iter) is want
