@@ -23,9 +23,19 @@ namespace skip {
 
 constexpr int kProjNT = 256;       // output columns per tile (8 waves x 32)
 constexpr int kProjKS = 32;        // columns of d per step
-constexpr int kProjRing = 5;       // row tiles in LDS (the direct loads address 64 KiB)
-constexpr int kProjAhead = 4;      // steps from the request of a row tile to its use
-constexpr int kProjWD = 4;         // the same of weights
+constexpr int kProjThreads = 512;
+// 96-row tiles (3072 kept rows make 32, so with 16 column tiles 512 items fill
+// 256 CUs twice over)
+constexpr int kProjMT = 96;
+constexpr int kProjMB = kProjMT / 32;     // 32-row blocks per tile
+constexpr int kProjRing = 4;
+constexpr int kProjAhead = 3;
+// 192-row tiles
+constexpr int kWideRows = 192;
+constexpr int kWideThreads = 256;
+constexpr int kWideRing = 5;       // row tiles in LDS (the direct loads address 64 KiB)
+constexpr int kWideAhead = 4;      // steps from the request of a row tile to its use
+constexpr int kWideWD = 4;         // the same of weights
 constexpr int kProjPackBlocks = 1024;
 
 // Packed order: for column tile nt, wave w, step s, k16 sub-step kk and lane
@@ -64,36 +74,161 @@ __device__ __forceinline__ size_t source_row(int r, const int32_t* __restrict__ 
   return (size_t)lo * N + clampi(kept_idx[r], 0, N - 1);
 }
 
-// Tile of a workgroup: 32 MB rows x 256 columns; 8 / NB waves, each 32 NB columns
-// of all rows.  Beside the matrix cores the bytes a CU draws from the L2 and
-// reads from LDS bound the kernel: 2 MB + 16 KiB of rows and weights per
-// 32-column step, and every wave reads the whole row tile.
-//   * MB = 6, NB = 2: the fewest bytes per product; one wave per SIMD, 192
-//     accumulators each (3072 rows of 4096 x 4096: 120 -> 105 us);
-//   * MB = 3, NB = 1: two workgroups a CU, finer items for the counts that do
-//     not fill whole rounds of the former (wide_tiles).
 // Work items are dealt to XCDs in runs (the hardware sends workgroup id L to
-// XCD L % 8): item = (L % 8) * per_xcd + L / 8, row tile fastest, so the items
-// of one XCD share their weight tiles in its L2.
-//
-// Few waves cover the latencies, so the loads run far ahead: row tiles are
-// requested kProjAhead steps before their use and published one step early, so
-// that the first operands of a step are read during the step before; weights
-// are requested kProjWD steps ahead, each k16 sub-step's as soon as its
-// products have read the registers (a wave waits for its loads in the order it
-// issued them, and the compiler counts these but not the direct loads: its
-// counted waits then only reach loads that are steps old).
-template <int MB, int NB, bool IDX, bool OUT_F32>
-__global__ void __launch_bounds__(512 / NB, MB == 3 ? 4 / NB : 2 / NB)
+// XCD L % 8): item = (L % 8) * per_xcd + L / 8, row tile fastest, so the
+// items of one XCD share their weight tiles in its L2.
+template <bool IDX, bool OUT_F32>
+__global__ void __launch_bounds__(kProjThreads)
 proj_gemm_kernel(const bf16_t* __restrict__ rows, const int32_t* __restrict__ kept_offsets,
                  const int32_t* __restrict__ kept_idx, int B, int N, int M, int d, int d_out,
                  const u32x4* __restrict__ Wp, void* __restrict__ Y, int n_items) {
-  constexpr int WD = kProjWD, AH = kProjAhead;
-  constexpr int MT = 32 * MB;                         // rows per tile
+  constexpr int A_ELEMS = kProjMT * kProjKS;          // 3072 (6 KiB)
+  __shared__ __attribute__((aligned(1024))) bf16_t Ar[kProjRing * A_ELEMS];
+
+  const int per_xcd = gridDim.x / 8;
+  const int item = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (item >= n_items) return;
+  const int MTL = (M + kProjMT - 1) / kProjMT;
+  const int mt = item % MTL, nt = item / MTL;
+  const int i0 = mt * kProjMT, j0 = nt * kProjNT;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int ksteps = d / kProjKS;
+  const int hh = lane >> 5, r32 = lane & 31;
+
+  // this thread's 16 bytes of a row tile: row tid/4 of the tile, physical
+  // chunk tid%4 holding logical chunk lc (XOR-swizzled by (row/2) % 4, so the
+  // operand reads of 8 consecutive rows hit distinct banks)
+  const int trow = tid >> 2;
+  const int lc = (tid & 3) ^ ((trow >> 1) & 3);
+  const size_t rid = source_row<IDX>(min(i0 + trow, M - 1), kept_offsets, kept_idx, B, N, M);
+  const bf16_t* asrc = rows + rid * d + lc * 8;
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+  const uint32_t ar_lds = lds_addr(Ar) + (uint32_t)(wave_s * 1024);
+  // (waves past the tile's rows, 4 * kProjMT threads and up, copy nothing)
+  const bool a_loader = tid < 4 * kProjMT;
+  auto issue_a = [&](int s) {
+    if (a_loader)
+      lds_dma16(asrc + s * kProjKS, __builtin_amdgcn_readfirstlane(
+                                     ar_lds + (uint32_t)((s % kProjRing) * A_ELEMS * 2)));
+  };
+  const u32x4* wsrc = Wp + ((size_t)(nt * 8 + wave) * ksteps) * 128 + lane;
+  auto load_w = [&](int s, u32x4 (&w)[2]) {
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) w[kk] = wsrc[(size_t)s * 128 + kk * 64];
+  };
+
+  f32x16_t acc[kProjMB];
+#pragma unroll
+  for (int mb = 0; mb < kProjMB; ++mb)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[mb][v] = 0.f;
+
+  int aoff[2][kProjMB];
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+    for (int mb = 0; mb < kProjMB; ++mb) {
+      const int row = mb * 32 + r32;
+      aoff[kk][mb] = row * kProjKS + (((2 * kk + hh) ^ ((row >> 1) & 3)) << 3);
+    }
+
+  auto mma_step = [&](int s, const u32x4 (&w)[2]) {
+    __builtin_amdgcn_sched_barrier(0);
+    const bf16_t* At = Ar + (s % kProjRing) * A_ELEMS;
+    u32x4 a[2][kProjMB];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int mb = 0; mb < kProjMB; ++mb) a[kk][mb] = *reinterpret_cast<const u32x4*>(At + aoff[kk][mb]);
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int mb = 0; mb < kProjMB; ++mb) acc[mb] = mfma32_bf16(a[kk][mb], w[kk], acc[mb]);
+    // half the operand reads ahead, then one MFMA per read
+    constexpr int NR = 2 * kProjMB;          // operand reads (= MFMAs)
+    __builtin_amdgcn_sched_group_barrier(0x100, NR / 2, 0);
+#pragma unroll
+    for (int i = 0; i < NR / 2; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, NR / 2, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+#pragma unroll
+  for (int a = 0; a < kProjAhead; ++a)
+    if (a < ksteps) issue_a(a);
+  u32x4 wA[2], wB[2];
+  load_w(0, wA);
+  load_w(min(1, ksteps - 1), wB);
+
+  // Step s: wait for the row tile of step s (outstanding after the wait: the
+  // tiles of steps s+1, s+2 while they exist, and the fragments of step s+1),
+  // barrier (publishes it; the slot of step s-1 is free), load the tile of
+  // step s+3, multiply step s, load the fragments of step s+2.
+  auto step = [&](int s, u32x4 (&w)[2]) {
+    if (s + 2 < ksteps) wait_vmcnt<4>();
+    else if (s + 1 < ksteps) wait_vmcnt<3>();
+    else wait_vmcnt<2>();
+    barrier_nofence();
+    if (s + kProjAhead < ksteps) issue_a(s + kProjAhead);
+    mma_step(s, w);
+    // unconditional (the last steps reload the final fragments): a
+    // conditional load would make the compiler drain the queue before the
+    // next use of w
+    load_w(min(s + 2, ksteps - 1), w);
+  };
+  int s = 0;
+  for (; s + 1 < ksteps; s += 2) {
+    step(s, wA);
+    step(s + 1, wB);
+  }
+  if (s < ksteps) step(s, wA);
+
+  // Accumulator element v of block mb: row mb*32 + 8*(v/4) + 4*hh + v%4,
+  // column j0 + 32*wave + r32.
+  const int j = j0 + wave * 32 + r32;
+#pragma unroll
+  for (int mb = 0; mb < kProjMB; ++mb)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int row = i0 + mb * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
+      if (row < M) {
+        if (OUT_F32)
+          static_cast<float*>(Y)[(size_t)row * d_out + j] = acc[mb][v];
+        else
+          static_cast<bf16_t*>(Y)[(size_t)row * d_out + j] = (bf16_t)f32_to_bf16(acc[mb][v]);
+      }
+    }
+}
+
+// Many rows of wide matrices (proj_wide_tiles): 192 rows x 256 columns a workgroup,
+// four waves of 64 columns.  Beside the matrix cores the bytes a CU draws from
+// the L2 and reads from LDS bound the GEMM: 28 KiB of rows and weights per
+// 32-column step here, for twice the products of the tile above with its 22 KiB,
+// and every wave reads the whole row tile.  Items as above.
+//
+// Few waves cover the latencies, so the loads run far ahead: row tiles are
+// requested kWideAhead steps before their use and published one step early, so
+// that the first operands of a step are read during the step before; weights
+// are requested kWideWD steps ahead, each k16 sub-step's as soon as its
+// products have read the registers (a wave waits for its loads in the order it
+// issued them, and the compiler counts these but not the direct loads: its
+// counted waits then only reach loads that are steps old).
+template <bool IDX, bool OUT_F32>
+__global__ void __launch_bounds__(kWideThreads, 1)
+proj_wide_kernel(const bf16_t* __restrict__ rows, const int32_t* __restrict__ kept_offsets,
+                 const int32_t* __restrict__ kept_idx, int B, int N, int M, int d, int d_out,
+                 const u32x4* __restrict__ Wp, void* __restrict__ Y, int n_items) {
+  constexpr int MB = kWideRows / 32, NB = 8 / (kWideThreads / 64);
+  constexpr int WD = kWideWD, AH = kWideAhead;
+  constexpr int MT = kWideRows;
   constexpr int A_ELEMS = MT * kProjKS;
   constexpr int WCH = 16 * MB * NB;                   // 16-byte chunks of a tile per wave
   constexpr int NI = (WCH + 63) / 64;                 // direct loads they take
-  __shared__ __attribute__((aligned(1024))) bf16_t Ar[kProjRing * A_ELEMS];
+  __shared__ __attribute__((aligned(1024))) bf16_t Ar[kWideRing * A_ELEMS];
   static_assert(sizeof(Ar) <= 65536, "direct loads address 64 KiB of LDS");
 
   const int per_xcd = gridDim.x / 8;
@@ -128,7 +263,7 @@ proj_gemm_kernel(const bf16_t* __restrict__ rows, const int32_t* __restrict__ ke
       if (q * 64 + lane < WCH)
         lds_dma16(asrc[q] + s * kProjKS,
                   __builtin_amdgcn_readfirstlane(
-                      ar_lds + ((uint32_t)s % kProjRing) * (A_ELEMS * 2) + q * 1024));
+                      ar_lds + ((uint32_t)s % kWideRing) * (A_ELEMS * 2) + q * 1024));
   };
   // weight fragments of this wave's 32-column blocks, [kk][nb] per step
   const u32x4* wsrc = Wp + ((size_t)(nt * 8 + wave * NB) * ksteps) * 128 + lane;
@@ -152,7 +287,7 @@ proj_gemm_kernel(const bf16_t* __restrict__ rows, const int32_t* __restrict__ ke
   for (int kk = 0; kk < 2; ++kk)
     aoff[kk] = r32 * kProjKS + (((2 * kk + hh) ^ ((r32 >> 1) & 3)) << 3);
   auto read_a = [&](int s, int kk, u32x4 (&a)[MB]) {
-    const bf16_t* At = Ar + ((uint32_t)s % kProjRing) * A_ELEMS + aoff[kk];
+    const bf16_t* At = Ar + ((uint32_t)s % kWideRing) * A_ELEMS + aoff[kk];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
       a[mb] = *reinterpret_cast<const u32x4*>(At + mb * 32 * kProjKS);
@@ -193,7 +328,7 @@ proj_gemm_kernel(const bf16_t* __restrict__ rows, const int32_t* __restrict__ ke
   // first operands of step s+1 (past the last step: stale values that nothing
   // uses).  The tail steps (after the last whole group of WD; every tile is
   // requested by then) load nothing and wait for all.
-  static_assert(AH >= WD && AH < kProjRing, "tail steps request no tile; a slot is free");
+  static_assert(AH >= WD && AH < kWideRing, "tail steps request no tile; a slot is free");
   constexpr int WQ = (AH - 1) * 2 * NB;
   auto step = [&](int s, u32x4 (&ws)[2][NB], auto tail) {
     constexpr bool TAIL = decltype(tail)::value;
@@ -359,18 +494,28 @@ hipError_t launch_proj_pack(int d, int d_out, const void* W, void* packed, hipSt
 
 constexpr long long kProjCUs = 256;
 
-// One 96 x 32 item per CU: 160 rows of 4096 x 4096 40 us against 47 on 96 x 256
-// tiles and 15 more to pack the weights; 768 rows of 1024 x 1024 15.6 against
-// 17.6.  At two rounds the tiles win (640 rows of 4096 x 4096: 140 us, 50).
-static bool few_rows(int M, int d_out) {
-  return (long long)((M + kFewRows - 1) / kFewRows) * (d_out / 32) <= kProjCUs;
+// At most one 96 x 32 item per CU, and a contraction long enough to split: its
+// eight parts and their sum cost about 11.7 us of back-to-back calls whatever d
+// is (one row 5.4, 40 rows 8.0), the 96-row tiles grow with d.  Packed weights,
+// 160 rows x 1024 columns, this form against tiles: d = 512 11.8 us against 9.0,
+// 768 11.8 against 11.4, 1024 11.8 against 13.9, 4096 0.66 of the tiles; 40 rows:
+// d = 512 8.0 against 8.6; one row: d = 256 5.3 against 5.8.  At two rounds of
+// items the tiles win (d = 4096: 1.2 times), and so they do on few columns of
+// many rows (3072 rows x 256: 1.04 to 1.12).  The same line with and without packed
+// weights: both calls give the same bits.
+bool proj_few_rows(int M, int d, int d_out) {
+  return d >= (M < 98 ? 240 + 8 * M : 1024) && M <= 24 * kFewRows &&
+         (long long)((M + kFewRows - 1) / kFewRows) * (d_out / 32) <= kProjCUs;
 }
 
 // 192-row tiles, one per CU and round, where whole rounds cost at most an
-// eighth more row blocks than 96-row tiles, two per CU (3072 rows of 4096 x
-// 4096, one round: 99 us against 116; 12288 rows 384 against 411; 6680 rows of
-// 2048 x 2048, 280 tiles in two rounds: 94 against 79).
-static bool wide_tiles(int M, int d_out) {
+// eighth more row blocks than 96-row tiles, two per CU (6680 rows of 2048 x
+// 2048, 280 tiles in two rounds: 94 us against 79), and the contraction is long
+// enough for loads that run four steps ahead: 192- over 96-row tiles, over the
+// sizes of whole rounds, 0.85-0.97 from d = 3072 on, 0.95-1.01 at 2048, 0.98-1.06
+// at 1536, 1.02-1.14 at 1024 and up to 2.1 at 64.
+bool proj_wide_tiles(int M, int d, int d_out) {
+  if (d < 2048) return false;
   const long long nt = d_out / kProjNT;
   const long long n96 = (M + 95) / 96 * nt, n192 = (M + 191) / 192 * nt;
   const long long rounds = (n192 + kProjCUs - 1) / kProjCUs;
@@ -402,27 +547,28 @@ hipError_t launch_proj_gemm(const skip_problem_t& p, const void* rows, const int
   const int M = p.total_kept;
   if (M <= 0) return hipSuccess;
   const bf16_t* R = static_cast<const bf16_t*>(rows);
-  if (few_rows(M, d_out))
+  if (proj_few_rows(M, p.d, d_out))
     return launch_proj_few<true>(p, R, kept_offsets, kept_idx, static_cast<const bf16_t*>(packed),
                                  d_out, Y, out_f32, s);
   const u32x4* Wc = static_cast<const u32x4*>(packed);
-  auto go = [&](auto mbc, auto nbc, auto idx, auto f32) -> hipError_t {
-    constexpr int MB = decltype(mbc)::value, NB = decltype(nbc)::value;
-    const int n_items = ((M + 32 * MB - 1) / (32 * MB)) * (d_out / kProjNT);
-    hipLaunchKernelGGL((proj_gemm_kernel<MB, NB, decltype(idx)::value, decltype(f32)::value>),
-                       dim3((n_items + 7) / 8 * 8), dim3(512 / NB), 0, s, R,
-                       kept_offsets, kept_idx, p.B, p.N, M, p.d, d_out, Wc, Y, n_items);
+  const bool wide = proj_wide_tiles(M, p.d, d_out);
+  const int rt = wide ? kWideRows : kProjMT;
+  const int n_items = ((M + rt - 1) / rt) * (d_out / kProjNT);
+  auto go = [&](auto idx, auto f32) -> hipError_t {
+    constexpr bool IDX = decltype(idx)::value, F32 = decltype(f32)::value;
+    const dim3 grid((n_items + 7) / 8 * 8);
+    if (wide)
+      hipLaunchKernelGGL((proj_wide_kernel<IDX, F32>), grid, dim3(kWideThreads), 0, s, R,
+                         kept_offsets, kept_idx, p.B, p.N, M, p.d, d_out, Wc, Y, n_items);
+    else
+      hipLaunchKernelGGL((proj_gemm_kernel<IDX, F32>), grid, dim3(kProjThreads), 0, s, R,
+                         kept_offsets, kept_idx, p.B, p.N, M, p.d, d_out, Wc, Y, n_items);
     return hipGetLastError();
   };
-  auto by_form = [&](auto mb, auto nb) -> hipError_t {
-    using T = std::true_type;
-    using F = std::false_type;
-    if (kept_idx) return out_f32 ? go(mb, nb, T{}, T{}) : go(mb, nb, T{}, F{});
-    return out_f32 ? go(mb, nb, F{}, T{}) : go(mb, nb, F{}, F{});
-  };
-  if (wide_tiles(M, d_out))
-    return by_form(std::integral_constant<int, 6>{}, std::integral_constant<int, 2>{});
-  return by_form(std::integral_constant<int, 3>{}, std::integral_constant<int, 1>{});
+  using T = std::true_type;
+  using F = std::false_type;
+  if (kept_idx) return out_f32 ? go(T{}, T{}) : go(T{}, F{});
+  return out_f32 ? go(F{}, T{}) : go(F{}, F{});
 }
 
 // Passage keys as bf16 rows for the projection: k~ = the bf16 rounding
@@ -451,7 +597,7 @@ hipError_t launch_project(const skip_problem_t& p, const void* rows, const int32
                           const int32_t* kept_idx, const void* W, int d_out, void* Y,
                           int out_f32, void* scratch, hipStream_t s) {
   if (p.total_kept <= 0) return hipSuccess;
-  if (few_rows(p.total_kept, d_out))
+  if (proj_few_rows(p.total_kept, p.d, d_out))
     return launch_proj_few<false>(p, static_cast<const bf16_t*>(rows), kept_offsets, kept_idx,
                                   static_cast<const bf16_t*>(W), d_out, Y, out_f32, s);
   hipError_t e = launch_proj_pack(p.d, d_out, W, scratch, s);

@@ -87,6 +87,9 @@ hipError_t launch_gate(const skip_problem_t& p, const skip_skv_gate_t& gt,
 
 // Learned projection of the kept rows --------------------------------------
 size_t proj_scratch_bytes(int d, int d_out);
+// which form multiplies M rows: the split contraction; else 192-row tiles; else 96
+bool proj_few_rows(int M, int d, int d_out);
+bool proj_wide_tiles(int M, int d, int d_out);
 hipError_t launch_proj_pack(int d, int d_out, const void* W, void* packed, hipStream_t s);
 hipError_t launch_proj_gemm(const skip_problem_t& p, const void* rows, const int32_t* kept_offsets,
                             const int32_t* kept_idx, const void* packed, int d_out, void* Y,

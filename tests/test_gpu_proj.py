@@ -138,14 +138,14 @@ def test_project_packed_matches_one_call(B, d_out):
             assert torch.equal(one, two) and torch.equal(one, three), (seed, out_f32)
 
 
-@pytest.mark.parametrize("d", [32, 64, 96, 160, 320])
+@pytest.mark.parametrize("d", [32, 64, 96, 160, 320, 1024, 1056, 2048, 2080, 2112, 2144])
 @pytest.mark.parametrize("M,d_out", [(1, 256), (95, 256), (97, 512), (97, 8192), (193, 8192),
                                      (100, 65536), (192, 65536), (484, 65536)])
 def test_project_tile_edges(B, M, d_out, d):
-    """Few rows (waves split the contraction, some without a part of it), tiles
-    of 96 and of 192 rows (the last three), with remainders of rows and of
-    steps: gathered rows, both outputs, packed and one-call, against float64
-    within the bound above."""
+    """Tiles of 96 rows, of 192 (the last three, from d = 2048 on) and the split
+    contraction (the first three, from d = 1024 on; one row from d = 256 on),
+    with remainders of rows, of steps and of the split's parts: gathered rows,
+    both outputs, packed and one-call, against float64 within the bound above."""
     say(f"projection tiles M={M} d_out={d_out} d={d}")
     g = torch.Generator(device="cuda")
     g.manual_seed(M + d)

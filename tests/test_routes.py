@@ -79,6 +79,32 @@ def test_regions_on_the_gram_matrix(want, B, k, H, r_max, n_iter):
     assert by_gram(problem(B=B, k_max=k, H=H), r_max, n_iter) is want
 
 
+@pytest.mark.parametrize("want,M,d,d_out", [
+    ("few", 160, 4096, 4096),
+    ("few", 1, 256, 8192),
+    ("tile", 16, 256, 256),                          # a short contraction is not split
+    ("few", 16, 384, 256),
+    ("tile", 96, 512, 256),
+    ("tile", 160, 768, 768),
+    ("few", 97, 1024, 1024),
+    ("few", 768, 1024, 1024),
+    ("tile", 769, 1024, 1024),                       # 288 items
+    ("tile", 3072, 1024, 256),
+    ("wide", 3072, 4096, 4096),
+    ("wide", 12288, 2048, 2048),
+    ("tile", 12288, 1536, 1024),                     # too short for loads far ahead
+    ("tile", 9000, 1024, 1024),
+    ("tile", 24000, 256, 256),
+    ("tile", 6680, 2048, 2048),                      # 280 wide tiles: a nearly empty round
+])
+def test_forms_of_the_projection(want, M, d, d_out):
+    few, wide = (B.LIB["_ZN4skip%sEiii" % n] for n in ("13proj_few_rows", "15proj_wide_tiles"))
+    for f in (few, wide):
+        f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_int] * 3
+    got = "few" if few(M, d, d_out) else "wide" if wide(M, d, d_out) else "tile"
+    assert got == want
+
+
 def test_the_benchmark_names_the_kernel_by_the_same_rule():
     import bench
     for kw in (dict(B=8), dict(B=9), dict(B=8, L_max=257), dict(B=64, dtype="f32")):
