@@ -192,23 +192,42 @@ topk_kernel(const double* __restrict__ z, const int32_t* __restrict__ kept_offse
 }
 
 // ---------------------------------------------------------------------------
-// V_kept[r] = V[b][kept_idx[r]]: one wave a row, four 16-byte chunks a lane in
-// flight.  Bound by latency: a wave that copied four rows of d = 2048 one after
-// another took 11.0 us for 6 questions of 41..334 rows, this 5.2.
-constexpr int kGatherRows = 4;     // per workgroup
+// V_kept[r] = V[b][kept_idx[r]], four 16-byte chunks a lane in flight: of one row
+// a wave, or, where a row has at most 64 chunks, one of each of R = 4 rows.
+// Bound by latency: a wave that copied four rows of d = 2048 one after another
+// took 11.0 us for 6 questions of 41..334 rows, this 5.2.  Many short rows are
+// bound by the waves' launch: 64 000 bfloat16 rows of d = 64 a wave each 16 us,
+// four a wave 9.6.
+constexpr int kGatherWaves = 4;    // per workgroup
 
-template <typename T>
-__global__ void __launch_bounds__(256)
+template <typename T, int R>
+__global__ void __launch_bounds__(64 * kGatherWaves)
 gather_kernel(const T* __restrict__ V, const int32_t* __restrict__ kept_offsets,
               const int32_t* __restrict__ kept_idx, int N, int d, int total_kept,
               T* __restrict__ V_kept) {
   constexpr int VEC = Vec16<T>::n, U = 4;
+  static_assert(R == 1 || R == U, "chunks of one row, or one of each row");
   const int b = blockIdx.y;
   int k0, k1;
   range_of(kept_offsets, b, total_kept, k0, k1);
   const int lane = threadIdx.x & 63;
-  const int r = k0 + blockIdx.x * kGatherRows + (threadIdx.x >> 6);
+  const int r = k0 + (blockIdx.x * kGatherWaves + (threadIdx.x >> 6)) * R;
   if (r >= k1) return;
+  if constexpr (R == U) {
+    int id[R];                     // rows past the question repeat its last one
+#pragma unroll
+    for (int u = 0; u < R; ++u) id[u] = kept_idx[min(r + u, k1 - 1)];
+    const int c = lane * VEC;
+    if (c >= d) return;
+    u32x4 x[R];
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+      x[u] = *reinterpret_cast<const u32x4*>(V + ((size_t)b * N + clampi(id[u], 0, N - 1)) * d + c);
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+      if (r + u < k1) *reinterpret_cast<u32x4*>(V_kept + (size_t)(r + u) * d + c) = x[u];
+    return;
+  }
   const T* from = V + ((size_t)b * N + clampi(kept_idx[r], 0, N - 1)) * d;
   T* to = V_kept + (size_t)r * d;
   for (int c = lane * VEC; c < d; c += U * 64 * VEC) {
@@ -278,14 +297,18 @@ hipError_t launch_gather(const skip_problem_t& p, const void* V,
                          const int32_t* kept_offsets, const int32_t* kept_idx,
                          void* V_kept, hipStream_t s) {
   if (p.k_max <= 0) return hipSuccess;
-  dim3 grid((p.k_max + kGatherRows - 1) / kGatherRows, p.B);
+  auto go = [&](auto tag, auto kernel, int rows) -> hipError_t {
+    using T = decltype(tag);
+    rows *= kGatherWaves;
+    hipLaunchKernelGGL(kernel, dim3((p.k_max + rows - 1) / rows, p.B), dim3(64 * kGatherWaves), 0,
+                       s, (const T*)V, kept_offsets, kept_idx, p.N, p.d, p.total_kept, (T*)V_kept);
+    return hipGetLastError();
+  };
   if (p.dtype == SKIP_F32)
-    hipLaunchKernelGGL(gather_kernel<float>, grid, dim3(256), 0, s, (const float*)V,
-                       kept_offsets, kept_idx, p.N, p.d, p.total_kept, (float*)V_kept);
-  else
-    hipLaunchKernelGGL(gather_kernel<bf16_t>, grid, dim3(256), 0, s, (const bf16_t*)V,
-                       kept_offsets, kept_idx, p.N, p.d, p.total_kept, (bf16_t*)V_kept);
-  return hipGetLastError();
+    return p.d <= 64 * Vec16<float>::n ? go(float{}, gather_kernel<float, 4>, 4)
+                                       : go(float{}, gather_kernel<float, 1>, 1);
+  return p.d <= 64 * Vec16<bf16_t>::n ? go(bf16_t{}, gather_kernel<bf16_t, 4>, 4)
+                                      : go(bf16_t{}, gather_kernel<bf16_t, 1>, 1);
 }
 
 }  // namespace skip

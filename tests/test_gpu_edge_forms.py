@@ -57,3 +57,19 @@ def test_pooling_batches_of_rows(B, dtype, rows):  # noqa: F811
         Qh, batch.kept_offsets, batch.Kh, batch.Vh, batch.passage_offsets,
         batch.query_passages, batch.wl.scale, 1.5)
     check_graph(batch, rp, col, adj)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 8), ("bf16", 512), ("bf16", 520), ("bf16", 2568),
+                                     ("f32", 8), ("f32", 256), ("f32", 264), ("f32", 1288)])
+def test_gather_short_and_long_rows(B, dtype, d):  # noqa: F811
+    """Four rows a wave (up to 64 chunks of 16 bytes a row) or one: rows of one
+    chunk to one more than a whole batch, counts about the rows of a workgroup."""
+    batch = small_batch(dtype, 6, B=6, N=64, H=d // 8, d_h=8, k=(1, 3, 4, 5, 16, 17), P=(1,),
+                        L_p=(1,))
+    say(f"gather {dtype} d={d} k={batch.k.tolist()}")
+    db = B.to_device(batch)
+    idx, _, rows = B.prune_topk(db, want_scores=False)
+    idx, rows = idx.cpu().long(), rows.cpu()
+    for b in range(batch.B):
+        k0, k1 = int(batch.kept_offsets[b]), int(batch.kept_offsets[b + 1])
+        assert torch.equal(rows[k0:k1], batch.V[b][idx[k0:k1]]), f"q{b}"
