@@ -28,7 +28,9 @@ SOURCES = ["skip_api.hip", "prune.hip", "graph.hip", "attn.hip", "mlp.hip", "gat
 
 # Per-source flags.  attn.hip: no NaN ever arises in the attention (finite
 # inputs; masked logits are -inf and meet only max, exp2 and a finite
-# reference), so maxima need no NaN-quieting moves around them.
+# reference), so maxima need no NaN-quieting moves around them.  (Where a row
+# tile looks for one among its sums, it tests bits that the compiler cannot see
+# through.)
 SOURCE_FLAGS = {"attn.hip": ["-fno-honor-nans"]}
 
 FLAGS = [

@@ -464,7 +464,7 @@ edge_select_kernel(CandidateArgs ca,
     base += edges_of_question(kq, Pkq, rule, avg_degree, beta);
   }
 #pragma unroll
-  for (int sh = 32; sh >= 1; sh >>= 1) base += __shfl_xor(base, sh, kWave);
+  for (int x = 32; x >= 1; x >>= 1) base += __shfl_xor(base, x, kWave);
   uint32_t total;
   uint32_t pos = block_exclusive_scan(__popc(flags), scan_sh, &total);
   const long long cap = (long long)total_kept * P_max;

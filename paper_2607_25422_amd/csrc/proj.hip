@@ -6,11 +6,14 @@
 //
 //   proj_pack_kernel : W repacked in the order the GEMM's waves read it (one
 //                      1 KiB run per wave, step and k16 sub-step)
-//   proj_gemm_kernel : work item = (96 or 192 kept rows, 256 output columns);
-//                      the row tile arrives in an LDS ring by direct
-//                      global->LDS loads, rows gathered through kept_idx as
-//                      they are loaded; each wave's weight fragments come
-//                      straight from the packed copy into registers
+//   proj_gemm_kernel : work item = (96 kept rows, 256 output columns); the row
+//                      tile arrives in a 4-slot LDS ring by direct global->LDS
+//                      loads three 32-column steps ahead, rows gathered through
+//                      kept_idx as they are loaded; each wave's weight fragments
+//                      come straight from the packed copy into registers two
+//                      steps ahead; 8 waves of 32 output columns x 96 rows
+//   proj_wide_kernel : long contractions of many rows: 192 rows a work item,
+//                      loads further ahead
 //   proj_few_kernel  : few rows: work item = (96 kept rows, 32 output columns),
 //                      the contraction split over the workgroup's waves
 #include <algorithm>

@@ -16,6 +16,8 @@
 // stores); the last of them to finish (a counter) sums the partials in slice
 // order and assigns every row by argmin_r |c_r|^2 - 2 v_i . c_r, which is
 // |v_i - c_r|^2 less the row's own |v_i|^2.
+// Small questions of enough iterations take three launches instead, on the
+// products of their rows (region_gram_kernel, regions_by_gram).
 #include <algorithm>
 #include <type_traits>
 

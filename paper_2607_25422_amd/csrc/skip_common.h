@@ -190,12 +190,6 @@ __device__ __forceinline__ float wave_sum_f32(float v) {
   return v;
 }
 
-__device__ __forceinline__ float wave_max_f32(float v) {
-#pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) v = fmaxf(v, __shfl_xor(v, s, kWave));
-  return v;
-}
-
 // Exclusive prefix sum of one uint32 per thread across the whole block, in
 // thread order.  `sh` needs blockDim.x / 64 + 1 words.  Returns the exclusive
 // prefix and writes the block total to *total.  Contains __syncthreads().

@@ -144,8 +144,10 @@ hipError_t launch_csr_to_mask(const skip_problem_t& p, const int32_t* kept_offse
                               const int32_t* query_passages,
                               const int32_t* edge_rowptr, const int32_t* edge_col,
                               uint64_t* rowmask, hipStream_t s);
-// Workgroup ids of the bf16 attention launch (0 for fp32): the work list
-// takes one 16-byte record per id.
+// Workgroup ids of the sparse attention launch (0 for fp32): the work list
+// takes one 16-byte record per id.  The workspace holds it for every bf16
+// problem, also for those that go by row tiles and leave it unused, so that its
+// size does not depend on the rule.
 long long attn_plan_ids(const skip_problem_t& p);
 // Whether the attention runs without the work list (row tiles).
 bool attn_by_tiles(const skip_problem_t& p);
