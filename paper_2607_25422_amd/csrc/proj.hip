@@ -211,7 +211,9 @@ proj_gemm_kernel(const bf16_t* __restrict__ rows, const int32_t* __restrict__ ke
 // four waves of 64 columns.  Beside the matrix cores the bytes a CU draws from
 // the L2 and reads from LDS bound the GEMM: 28 KiB of rows and weights per
 // 32-column step here, for twice the products of the tile above with its 22 KiB,
-// and every wave reads the whole row tile.  Items as above.
+// and every wave reads the whole row tile.  Back-to-back calls with packed
+// weights of 4096 x 4096: 3072 rows 101 -> 93 us, 12288 rows 401 -> 370.  Items as
+// above.
 //
 // Few waves cover the latencies, so the loads run far ahead: row tiles are
 // requested kWideAhead steps before their use and published one step early, so
@@ -388,8 +390,8 @@ proj_wide_kernel(const bf16_t* __restrict__ rows, const int32_t* __restrict__ ke
 // wave order.  Operands come straight from memory into registers, four k16
 // groups in flight while four are multiplied: bound by the lines a CU draws
 // from the L2 (96 + 32 rows of d; a load touches 32 of them).  PACKED: W is
-// the packed copy; otherwise W itself, which saves the packing pass (160 keys
-// of 4096 x 4096: packing and product 68 -> 40 us).
+// the packed copy; otherwise W itself, which saves the packing pass (160 rows
+// of 4096 x 4096, back to back: tiles after packing 60 us, this 36).
 constexpr int kFewRows = 96;
 constexpr int kFewMB = kFewRows / 32;
 constexpr int kFewWaves = 8;
@@ -506,14 +508,17 @@ constexpr long long kProjCUs = 256;
 // items the tiles win (d = 4096: 1.2 times), and so they do on few columns of
 // many rows (3072 rows x 256: 1.04 to 1.12).  The same line with and without packed
 // weights: both calls give the same bits.
-bool proj_few_rows(int M, int d, int d_out) {
-  return d >= (M < 98 ? 240 + 8 * M : 1024) && M <= 24 * kFewRows &&
+static bool few_fit(int M, int d_out) {
+  return M <= 24 * kFewRows &&
          (long long)((M + kFewRows - 1) / kFewRows) * (d_out / 32) <= kProjCUs;
+}
+bool proj_few_rows(int M, int d, int d_out) {
+  return d >= (M < 98 ? 240 + 8 * M : 1024) && few_fit(M, d_out);
 }
 
 // 192-row tiles, one per CU and round, where whole rounds cost at most an
 // eighth more row blocks than 96-row tiles, two per CU (6680 rows of 2048 x
-// 2048, 280 tiles in two rounds: 94 us against 79), and the contraction is long
+// 2048, 280 tiles in two rounds: 88 us against 74), and the contraction is long
 // enough for loads that run four steps ahead: 192- over 96-row tiles, over the
 // sizes of whole rounds, 0.85-0.97 from d = 3072 on, 0.95-1.01 at 2048, 0.98-1.06
 // at 1536, 1.02-1.14 at 1024 and up to 2.1 at 64.
@@ -596,11 +601,15 @@ hipError_t launch_keys_bf16(const double* kbar, const float* given, size_t n, vo
   return hipGetLastError();
 }
 
+// keys: passage keys, which no packed call has to agree with, take the split
+// contraction at every d: W as it is and one launch instead of two (160 rows of
+// 256 x 1024: calls one after another 15.4 us against 17.7, bound by their
+// launches; captured 13.6 against 9.0).
 hipError_t launch_project(const skip_problem_t& p, const void* rows, const int32_t* kept_offsets,
                           const int32_t* kept_idx, const void* W, int d_out, void* Y,
-                          int out_f32, void* scratch, hipStream_t s) {
+                          int out_f32, void* scratch, hipStream_t s, bool keys) {
   if (p.total_kept <= 0) return hipSuccess;
-  if (proj_few_rows(p.total_kept, p.d, d_out))
+  if (keys ? few_fit(p.total_kept, d_out) : proj_few_rows(p.total_kept, p.d, d_out))
     return launch_proj_few<false>(p, static_cast<const bf16_t*>(rows), kept_offsets, kept_idx,
                                   static_cast<const bf16_t*>(W), d_out, Y, out_f32, s);
   hipError_t e = launch_proj_pack(p.d, d_out, W, scratch, s);

@@ -434,7 +434,7 @@ skip_status_t skip_project_passage_keys(const skip_problem_t* p, const void* Kh,
   // the keys are the rows of a plain (ungathered) projection
   skip_problem_t q = *p;
   q.total_kept = p->total_passages;
-  SKIP_TRY(launch_project(q, kb, nullptr, nullptr, W, d_out, keys_out, 1, packed, s));
+  SKIP_TRY(launch_project(q, kb, nullptr, nullptr, W, d_out, keys_out, 1, packed, s, true));
   return SKIP_OK;
 }
 

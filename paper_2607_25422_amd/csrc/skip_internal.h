@@ -98,7 +98,7 @@ hipError_t launch_keys_bf16(const double* kbar, const float* given, size_t n, vo
                             hipStream_t s);
 hipError_t launch_project(const skip_problem_t& p, const void* rows, const int32_t* kept_offsets,
                           const int32_t* kept_idx, const void* W, int d_out, void* Y,
-                          int out_f32, void* scratch, hipStream_t s);
+                          int out_f32, void* scratch, hipStream_t s, bool keys = false);
 
 // Regions of the kept tokens (k-means) ------------------------------------
 int region_slices(const skip_problem_t& p);
