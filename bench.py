@@ -141,6 +141,16 @@ def attention_kernel(p):
     return "attn_sparse_kernel", "hbm"
 
 
+def projection_kernel(rows, d, d_out):
+    """Name of the kernel that multiplies so many rows with packed weights
+    (skip::proj_few_rows, skip::proj_wide_tiles)."""
+    from paper_2607_25422_amd import binding as B
+    if B.LIB["_ZN4skip13proj_few_rowsEiii"](rows, d, d_out) & 1:
+        return "proj_few_kernel"
+    wide = B.LIB["_ZN4skip15proj_wide_tilesEiii"](rows, d, d_out) & 1
+    return "proj_wide_kernel" if wide else "proj_gemm_kernel"
+
+
 def measured_traffic(workload: str):
     """HBM bytes per attention launch from the committed counter summary, or
     None when it was taken on another workload or an older attention source."""
@@ -385,7 +395,8 @@ def bench_project(args):
                    "d_out": d_out, "seed": args.seed},
         "step_gpu_ms": {"p10": round(ms[n // 10], 5), "p50": round(ms[n // 2], 5),
                         "p90": round(ms[min(n - 1, 9 * n // 10)], 5)},
-        "roofline": {"kernel": "proj_gemm_kernel (weights packed once beforehand)",
+        "roofline": {"kernel": projection_kernel(p.total_kept, p.d, d_out) +
+                     " (weights packed once beforehand)",
                      "bound": "mfma", "achieved": round(tf_p, 1), "peak": BF16_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": round(tf_p / BF16_PEAK_TFLOPS, 4),
                      "traffic": None, "algorithmic_gflop": round(flops / 1e9, 2),

@@ -33,9 +33,10 @@ def test_kernels_that_store_to_lds_wait_for_their_stores(source, name):
     assert "barrier_nofence()" not in body and "builtin_amdgcn_s_barrier" not in body
 
 
-def test_the_plain_barrier_only_publishes_direct_loads():
-    """proj_gemm_kernel's one LDS array is filled by lds_dma16 alone."""
-    body = kernel_body("proj.hip", "proj_gemm_kernel")
+@pytest.mark.parametrize("name", ["proj_gemm_kernel", "proj_wide_kernel"])
+def test_the_plain_barrier_only_publishes_direct_loads(name):
+    """The projection tiles' one LDS array is filled by lds_dma16 alone."""
+    body = kernel_body("proj.hip", name)
     assert "barrier_nofence()" in body
     assert re.findall(r"__shared__[^;]*\b(\w+)\[", body) == ["Ar"]
     assert not re.search(r"\b(Ar|At)\b[^;=]*[^=!<>]=[^=]", body.replace("const bf16_t* At = Ar", ""))

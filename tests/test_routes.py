@@ -110,3 +110,5 @@ def test_the_benchmark_names_the_kernel_by_the_same_rule():
     for kw in (dict(B=8), dict(B=9), dict(B=8, L_max=257), dict(B=64, dtype="f32")):
         name = bench.attention_kernel(problem(**kw))[0]
         assert name == ("attn_tile_kernel" if by_tiles(problem(**kw)) else "attn_sparse_kernel")
+    for want, M, d in (("few", 160, 4096), ("wide", 3072, 4096), ("gemm", 3072, 1024)):
+        assert bench.projection_kernel(M, d, d) == f"proj_{want}_kernel"
