@@ -804,12 +804,15 @@ template <int D> struct TileOps<bf16_t, D> {
   __device__ static void clear_v(KV& x, int i) { x.v[i] = vword(0u); }
 };
 
-// Bound by the matrix cores at large batches (rows not adjacent to a passage
-// of their tile compute for nothing there; one wave per row and head, edges
-// only, on the vector units spent ten times as long) and by the wave's load
-// and product chain at small ones.  Measured against that form: 8 questions
-// of 96 rows, 16 heads of 64, 5 passages of 97-160 tokens 35.5 us (359); one
-// question of 96 rows, 4 heads of 64, 4 passages of 64 tokens 7.9 us (38.3).
+// Bound by the waves' chains of loads, products and softmax: on 768 float32
+// tiles of 640 tokens (8 questions of 96 rows, 16 heads of 64, 5 passages of
+// 97-160) the matrix cores are busy 38 % of the cycles, the waves wait 28 % of
+// theirs for loads and 57 % to issue, and two workgroups a CU make one and a half
+// rounds of it; on 768 bf16 tiles the matrix cores are busy 6 %.  Rows not
+// adjacent to a passage of their tile compute for nothing there, yet one wave per
+// row and head on the vector units, edges only, took ten times as long: that
+// batch 35.5 us (359); one question of 96 rows, 4 heads of 64, 4 passages of 64
+// tokens 8.1 us (38.3).
 constexpr int kTileRows = 16;
 // Workgroups from which four waves each fill the chip; below, eight shorten
 // the wave's chain (routes of 350 to 2304 workgroups: 134 us with four and
