@@ -29,7 +29,8 @@
  * Selection decisions (the kept set and the edge set) are computed from
  * float64 accumulations, so they match a float64 reference on any input whose
  * decisive gap exceeds float64 rounding.  Attention accumulates in float32;
- * in bf16 mode the softmax weights are rounded to bf16 before the PV product.
+ * in bf16 mode the softmax weights enter the PV product as pairs of bf16 values
+ * (to about 2^-16 relative).
  *
  * Conventions for every entry point
  *   - The caller owns all memory.  Every array argument is a DEVICE pointer

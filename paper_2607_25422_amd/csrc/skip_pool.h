@@ -167,6 +167,10 @@ pool_kernel(PoolRanges<T> qr, const T* __restrict__ w, PoolRanges<T> pr, int d,
 // another); 45 passages of 37..301 tokens, d = 2048, and 6 questions, 15.6 ->
 // 9.1 us each.  Many ranges are bound by HBM and keep the longer runs of a row:
 // 160 passages of 256 tokens, d = 4096 (640 workgroups), 60 us against 70.
+// Between 256 and 512 workgroups the first form wins by 0.77-0.98 over d = 256 ..
+// 8192 and 4 .. 1024 rows, except on ranges that start 2 MiB apart and meet in
+// the memory channels (256 rows of 8 KiB: 1.07-1.14 of a call that pools and
+// scores) and on 4 rows of one slice (1.03-1.08).
 constexpr long long kPoolFew = 512;
 
 // Questions (Qtok by q_offsets -> u, nq ranges) and passages (Kh by
