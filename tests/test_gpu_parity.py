@@ -252,9 +252,9 @@ def test_xattn_given_graph_and_keys(B, dtype):
     check_attention(f64(O2), f64(L2), np.concatenate(O2_ref), np.concatenate(L2_ref), dtype, "keys")
 
 
-# Kept-row counts that give every layout of a work item's rows: 1-8 blocks of
-# 32 rows (the item splits 1-2 and 5-6 blocks into token halves merged at the
-# end), and two items per question above 256 rows.
+# Kept-row counts about the edges of blocks of 16 and 32 rows and of chunks of
+# rows.  (Two heads of three questions go by row tiles; the sparse kernel's
+# layouts are in test_gpu_attn_sparse.py.)
 ROW_COUNTS = (1, 31, 33, 64, 65, 129, 160, 161, 193, 224, 256, 300, 450, 512)
 
 
